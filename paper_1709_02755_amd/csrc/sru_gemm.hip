@@ -1,4 +1,5 @@
-// Matrix products of the SRU layer on the gfx950 matrix cores (MFMA).
+// bf16 matrix products of the SRU layer on the gfx950 matrix cores (MFMA);
+// the fp32 ones are in sru_gemm_f32.hip.
 //
 // The forward projection of Sec. 3.1 (U = X [W; W_f; W_r]^T over all L*B
 // tokens at once) and the two products of the backward pass (dX = dU W and
@@ -6,10 +7,8 @@
 //     C[M,N] = sum_k A(m,k) B(n,k)
 // with each operand either K-contiguous ("KC": row-major [rows, K]) or
 // row-contiguous ("RC": [K, rows]), and stored as fp32 or bf16.  The loader
-// stages a tile into LDS in the compute type:
-//   * bf16 mode: bf16 operands are copied, fp32 ones rounded to bf16 (RNE,
-//     v_cvt_pk_bf16_f32); v_mfma_f32_32x32x16_bf16 with fp32 accumulation;
-//   * fp32 mode: v_mfma_f32_32x32x2_f32.
+// stages a tile into LDS in bf16: bf16 operands are copied, fp32 ones rounded
+// (RNE, v_cvt_pk_bf16_f32); v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
 // LDS always holds a tile K-contiguous per row ([rows][BK + 16 bytes]), so a
 // lane's MFMA fragment is one 16-byte LDS read.  An RC operand is transposed
 // in registers on its way into LDS: a thread owns a block of k-rows x rows,
@@ -31,28 +30,20 @@
 #include <type_traits>
 
 #include "sru_device.h"
+#include "sru_gemm_tile.h"
 #include "sru_internal.h"
-
 
 namespace sru {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, bool BF16_>
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_>
 struct Cfg {
   static constexpr int BM = BM_, BN = BN_, BK = BK_;
   static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int FM = WM / 32, FN = WN / 32;
   static constexpr int THREADS = WAVES_M * WAVES_N * 64;
-  static constexpr bool BF16 = BF16_;
-  static constexpr int ESZ = BF16 ? 2 : 4;    // bytes per LDS element
+  static constexpr int ESZ = 2;                // bytes per LDS element
   static constexpr int KPACK = 16 / ESZ;       // elements per 16-byte fragment read
   static constexpr int KSLAB = 2 * KPACK;      // k covered by one fragment pair
   static constexpr int LDK = BK + KPACK;       // LDS row stride (16 bytes of padding)
@@ -63,69 +54,7 @@ struct Cfg {
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile is a grid of 32x32 MFMA tiles");
 };
 
-// bf16: tiles 256x256x64, 4 waves of 128x128.  fp32: 128x128x32, 4 waves of 64x64.
-using CfgBF16 = Cfg<256, 256, 64, 2, 2, true>;
-using CfgF32 = Cfg<128, 128, 32, 2, 2, false>;
-
-// Source element types: fp32, or bf16 carried as raw 16-bit patterns.
-template <class S> struct Src;
-template <> struct Src<float> { static constexpr int E = 4; };     // elements per 16 bytes
-template <> struct Src<uint16_t> { static constexpr int E = 8; };
-
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  bf16x2 v;
-  v[0] = (__bf16)lo;  // RNE (v_cvt_pk_bf16_f32)
-  v[1] = (__bf16)hi;
-  return __builtin_bit_cast(unsigned, v);
-}
-
-// Vector loads go through a buffer resource: the hardware returns zeros for
-// any offset at or beyond its byte size, so an out-of-range chunk is loaded
-// from the sentinel offset kOOB instead of being masked afterwards (no select
-// on the loaded data, so nothing has to wait for it).  Operands must then be
-// smaller than kOOB bytes; the launcher checks this.
-constexpr unsigned kOOB = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
-  // dword 3 = 0x00020000: 32-bit data format, the raw-buffer setting of gfx9 parts
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
-                                           0x00020000);
-}
-
-// Resource for the bytes of an operand from `base` on (extent `bytes`),
-// its range capped below kOOB so that sentinel offsets stay out of range.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* p, long long base,
-                                                             long long bytes) {
-  return make_rsrc(static_cast<const unsigned char*>(p) + base,
-                   (unsigned)min(bytes - base, (long long)kOOB - 1));
-}
-
-__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-}
-
-// Element-wise variant for unaligned or ragged operands: element e is valid
-// when e < valid.
-template <class S>
-__device__ __forceinline__ u32x4 load16_elems(const S* src, long long idx, int valid) {
-  constexpr int E = Src<S>::E;
-  S tmp[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool ok = e < valid;
-    const S x = src[ok ? idx + e : 0];
-    tmp[e] = ok ? x : S(0);
-  }
-  return __builtin_bit_cast(u32x4, tmp);
-}
-
-// Element e of a 16-byte chunk as fp32.  The element is copied to a scalar
-// first: a bit cast applied directly to a vector-element lvalue reads element
-// 0 with this compiler.
-__device__ __forceinline__ float f32_of(const u32x4& v, int e) {
-  const unsigned x = v[e];
-  return __builtin_bit_cast(float, x);
-}
+using CfgBF16 = Cfg<256, 256, 64, 2, 2>;  // 4 waves of 128x128
 
 // ---- loader for a K-contiguous operand: element (r, k) at src[r*ld + k]
 template <class C, int R, class S, bool VEC>
@@ -134,7 +63,6 @@ struct LoaderKC {
   static constexpr int CPR = C::BK / E;  // 16-byte chunks per row
   static constexpr int PER = R * CPR / C::THREADS;
   static_assert(R * CPR % C::THREADS == 0, "tile must split evenly over the threads");
-  static_assert(C::BF16 || std::is_same<S, float>::value, "fp32 compute takes fp32 operands");
   u32x4 v[PER];
   unsigned base[PER];  // VEC: byte offset of the chunk at k = 0 (rows clamped)
 
@@ -171,7 +99,7 @@ struct LoaderKC {
       const int r = c / CPR;
       const int k = (c % CPR) * E;
       unsigned char* dst = lds + (r * C::LDK + k) * C::ESZ;
-      if constexpr (C::BF16 && std::is_same<S, float>::value) {
+      if constexpr (std::is_same<S, float>::value) {
         u32x2 w;
         w[0] = pack_bf16(f32_of(v[i], 0), f32_of(v[i], 1));
         w[1] = pack_bf16(f32_of(v[i], 2), f32_of(v[i], 3));
@@ -191,12 +119,11 @@ struct LoaderKC {
 template <class C, int R, class S, bool VEC>
 struct LoaderRC {
   static constexpr int E = Src<S>::E;              // rows per chunk
-  static constexpr int KB = C::BF16 ? 8 : 4;       // k per LDS write (16 bytes)
+  static constexpr int KB = 8;                     // k per LDS write (16 bytes)
   static constexpr int NKB = C::BK / KB;
   static constexpr int NMB = (R / E) * NKB;
   static constexpr int PER = NMB / C::THREADS;
   static_assert(NMB % C::THREADS == 0, "tile must split evenly over the threads");
-  static_assert(C::BF16 || std::is_same<S, float>::value, "fp32 compute takes fp32 operands");
   u32x4 v[PER][KB];
   unsigned base[PER];  // VEC: byte offset of k-row kb*KB at k0 = 0 (rows clamped)
 
@@ -242,10 +169,7 @@ struct LoaderRC {
       for (int e = 0; e < E; ++e) {
         unsigned char* dst = lds + ((r + e) * C::LDK + kb * KB) * C::ESZ;
         u32x4 w;
-        if constexpr (!C::BF16) {
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) w[kk] = v[i][kk][e];
-        } else if constexpr (std::is_same<S, float>::value) {
+        if constexpr (std::is_same<S, float>::value) {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             w[j] = pack_bf16(f32_of(v[i][2 * j], e), f32_of(v[i][2 * j + 1], e));
@@ -266,65 +190,6 @@ struct LoaderRC {
 template <class C, int R, bool KC, class S, bool VEC>
 using Loader =
     typename std::conditional<KC, LoaderKC<C, R, S, VEC>, LoaderRC<C, R, S, VEC>>::type;
-
-struct KernelArgs {
-  const void* A;
-  const void* B;
-  // operand extents in bytes: the register-staged kernels address whole
-  // operands through buffer resources (VEC: extents below kOOB); the direct
-  // kernel bases its resources at each workgroup's panels
-  long long a_bytes, b_bytes;
-  float* out;               // C, or the split partials
-  long long lda, ldb, ldo;
-  long long split_stride;   // elements between split outputs (0 when splits == 1)
-  int M, N, K;
-  int k_per_split;          // multiple of BK
-  int tiles_m, tiles_n, splits;
-  const float* add;
-  long long add_ld, add_off;
-  int add_count;
-  int vec_out;  // output (and addend) rows allow 16-byte accesses: see write_tile_rows
-  uint16_t* outb;  // bf16 copy of the result (direct kernel, OB), out may be nullptr
-  long long ldob;
-};
-
-// Epilogue shared by the kernels.  32x32 accumulator layout: element e of
-// lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 of the MFMA tile.
-// ADD = number of addend tensors (0..2, see KernelArgs).  For each MFMA
-// tile the addend loads are issued together (rows and columns clamped into
-// range, so no branch separates them) before the stores.
-template <class C, int ADD>
-__device__ __forceinline__ void write_tile_add(const KernelArgs& g,
-                                               const floatx16 (&acc)[C::FM][C::FN], int m0,
-                                               int n0, int wm0, int wn0, int lane, int split) {
-  float* out = g.out + (long long)split * g.split_stride;
-  const bool full = m0 + C::BM <= g.M && n0 + C::BN <= g.N;
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-      const int n = n0 + wn0 + j * 32 + (lane & 31);
-      const int mb = m0 + wm0 + i * 32 + (lane >> 5) * 4;
-      float v[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) v[e] = acc[i][j][e];
-      if constexpr (ADD > 0) {
-        const int nc = min(n, g.N - 1);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int mc = min(mb + (e >> 2) * 8 + (e & 3), g.M - 1);
-          const float* ar = g.add + (long long)mc * g.add_ld + nc;
-          v[e] += ar[0];
-          if constexpr (ADD > 1) v[e] += ar[g.add_off];
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = mb + (e >> 2) * 8 + (e & 3);
-        if (full || (m < g.M && n < g.N)) out[(long long)m * g.ldo + n] = v[e];
-      }
-    }
-}
 
 // Epilogue of the direct kernel, whose MFMAs take the B-operand fragment
 // first and so accumulate the transposed tile: element e of lane l is row
@@ -568,34 +433,6 @@ __device__ __forceinline__ void write_tile_staged(const KernelArgs& g,
   }
 }
 
-// XCD-aware remap of the linear workgroup id: workgroups are dispatched
-// round-robin over the 8 XCDs; each XCD gets a contiguous run of tiles.
-struct TileIdx {
-  int split, tm, tn;
-};
-__device__ __forceinline__ TileIdx tile_of(const KernelArgs& g) {
-  const int nwg = gridDim.x;
-  const int w = blockIdx.x;
-  const int q = nwg / 8, rmd = nwg % 8, x = w % 8;
-  const int u = x * q + (x < rmd ? x : rmd) + w / 8;
-  const int nt = g.tiles_m * g.tiles_n;
-  TileIdx r;
-  r.split = u / nt;
-  const int t = u - r.split * nt;
-  // tiles in groups of GM tile rows, column by column within a group: the
-  // 32 tiles an XCD runs at once then span 4 A panels x 8 B panels instead
-  // of 3 x 12 (gemm_u's 12 column tiles), fewer distinct panels in its L2
-  // (measured: GM = 4 slightly ahead of 8, 16 behind)
-  constexpr int GM = 4;
-  const int gsz = GM * g.tiles_n;
-  const int first = (t / gsz) * GM;
-  const int rows = min(g.tiles_m - first, GM);
-  const int tg = t - (t / gsz) * gsz;
-  r.tm = first + tg % rows;
-  r.tn = tg / rows;
-  return r;
-}
-
 template <class C, bool A_KC, bool B_KC, class SA, class SB, bool VEC, int ADD>
 __global__ __launch_bounds__(C::THREADS) void gemm_kernel(KernelArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES];
@@ -661,18 +498,9 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(KernelArgs g) {
       for (int i = 0; i < C::FM; ++i)
 #pragma unroll
         for (int j = 0; j < C::FN; ++j) {
-          if constexpr (C::BF16) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bfr[j]), acc[i][j],
-                0, 0, 0);
-          } else {
-            // Lane group h = lane/32 holds k = koff..koff+3 of its row; MFMA e
-            // takes element e, so the 4 MFMAs cover the 8 k of this slab once.
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][e], bfr[j][e], acc[i][j], 0,
-                                                               0, 0);
-          }
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bfr[j]), acc[i][j], 0,
+              0, 0);
         }
     }
     if (next) {
@@ -1507,8 +1335,6 @@ int splits_for(const GemmDesc& g) {
   if (g.a_kc && (!g.kc_split || tiles > 64)) return 1;
   const int kt = (g.K + C::BK - 1) / C::BK;  // K steps
   int s = (2 * 256 + tiles - 1) / tiles;     // aim for two workgroups per CU
-  // fp32 accumulation chains stay short (<= 2048 terms per split)
-  if (!C::BF16) s = max(s, (g.K + 2047) / 2048);
   s = min(s, max(1, kt / 4));                // at least 4 K steps per split
   return max(1, min(s, 64));
 }
@@ -1586,7 +1412,7 @@ hipError_t launch_cfg(const GemmDesc& g, hipStream_t st) {
                    vec_ok<SB>(g.B, g.ldb, B_KC ? g.K : g.N, b_bytes);
   a.a_bytes = vec ? a_bytes : 0;
   a.b_bytes = vec ? b_bytes : 0;
-  timing_before(g.label ? g.label : !g.b_kc ? (g.a_kc ? "gemm_nn" : "gemm_tn") : "gemm_nt", st);
+  timing_before(gemm_label(g), st);
   if (vec)
     launch_staged<C, A_KC, B_KC, SA, SB, true>(a, nwg, st);
   else
@@ -1780,7 +1606,7 @@ hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
               (a.add_count == 0 || (a.add_ld % 4 == 0 && a.add_off % 4 == 0 && al16(a.add))) &&
               (!OB || (a.ldob % 4 == 0 && ((uintptr_t)a.outb & 7) == 0));
   const int nwg = a.tiles_m * a.tiles_n * splits;
-  timing_before(g.label ? g.label : !g.b_kc ? (g.a_kc ? "gemm_nn" : "gemm_tn") : "gemm_nt", st);
+  timing_before(gemm_label(g), st);
   if constexpr (OB) launch_direct<C, 0, A_RC, B_RC, true>(a, nwg, st);
   else if constexpr (C::WN == 96) launch_direct<C, 0, A_RC, B_RC>(a, nwg, st);  // no addend
   else if (a.add_count == 2) launch_direct<C, 2, A_RC, B_RC>(a, nwg, st);
@@ -1793,21 +1619,19 @@ hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
 }
 
 // Operand-type combinations that are instantiated: fp32 x fp32 for every
-// layout in both compute modes, plus the bf16-operand products of the layer:
+// layout, plus the bf16-operand products of the layer:
 // U = X W^T (fp32 X, bf16 W), dX = dU W (bf16 dU, bf16 W^T, as NT) and
 // dW = dU^T X (bf16 dU, fp32 X).
 template <class C, bool A_KC, bool B_KC>
 hipError_t launch_types(const GemmDesc& g, hipStream_t st) {
   if (!g.a_bf16 && !g.b_bf16) return launch_cfg<C, A_KC, B_KC, float, float>(g, st);
-  if constexpr (C::BF16) {
-    if constexpr (A_KC && B_KC) {
-      if (!g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, float, uint16_t>(g, st);
-      if (g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, uint16_t, uint16_t>(g, st);
-    }
-    if constexpr (!A_KC && !B_KC) {
-      if (g.a_bf16 && !g.b_bf16) return launch_cfg<C, false, false, uint16_t, float>(g, st);
-      if (g.a_bf16 && g.b_bf16) return launch_cfg<C, false, false, uint16_t, uint16_t>(g, st);
-    }
+  if constexpr (A_KC && B_KC) {
+    if (!g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, float, uint16_t>(g, st);
+    if (g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, uint16_t, uint16_t>(g, st);
+  }
+  if constexpr (!A_KC && !B_KC) {
+    if (g.a_bf16 && !g.b_bf16) return launch_cfg<C, false, false, uint16_t, float>(g, st);
+    if (g.a_bf16 && g.b_bf16) return launch_cfg<C, false, false, uint16_t, uint16_t>(g, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1826,8 +1650,9 @@ bool gemm_is_direct(const GemmDesc& g) { return direct_ok(g); }
 
 int gemm_splits(const GemmDesc& g) {
   if (direct_ok(g)) return direct_splits(g);
-  const int s = g.bf16 ? splits_for<CfgBF16>(g) : splits_for<CfgF32>(g);
-  const int bk = g.bf16 ? CfgBF16::BK : CfgF32::BK;
+  if (!g.bf16) return gemm_f32_splits(g);
+  const int s = splits_for<CfgBF16>(g);
+  const int bk = CfgBF16::BK;
   const int kt = (g.K + bk - 1) / bk;
   const int kps = ((kt + s - 1) / s) * bk;
   return (g.K + kps - 1) / kps;
@@ -1855,7 +1680,9 @@ hipError_t gemm_launch(const GemmDesc& g, hipStream_t st) {
     return launch_direct_cfg<CfgDirectKC, false, false>(g, st);
   }
   if (g.Cb) return hipErrorInvalidValue;  // a bf16 result needs the direct path
-  return g.bf16 ? launch_layout<CfgBF16>(g, st) : launch_layout<CfgF32>(g, st);
+  if (g.bf16) return launch_layout<CfgBF16>(g, st);
+  if (hipError_t e = gemm_f32_launch(g, st)) return e;
+  return finish_product(g, gemm_f32_splits(g), st);
 }
 
 template <class S>

@@ -1,0 +1,619 @@
+// fp32 matrix products on the bf16 matrix units (gfx950).
+//
+//     C[M,N] = sum_k A(m,k) B(n,k),  A, B, C fp32
+//
+// The fp32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at a sixteenth
+// of the bf16 one's rate.  An fp32 value is exactly the sum of three bf16
+// values: a = a1 + a2 + a3 with a1 = bf16(a), a2 = bf16(a - a1),
+// a3 = a - a1 - a2 (24 significant bits in three signed parts of 8; both
+// differences are exact).  A product then takes six bf16 matrix
+// instructions, every term down to 2^-16 of the largest:
+//     a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + O(2^-26 |a b|)
+// each an exact product of 8-bit significands summed in fp32: the terms left
+// out are a quarter of fp32's own rounding, and a 16-k slab is rounded into
+// the accumulator 6 times instead of 8.
+//
+// The matrix instruction rounds to nearest, but where its products exceed
+// the accumulator it drops the accumulator's low bits, always downwards: a
+// sum comes out about 1e-8 of its scale too small, a tenth of its rounding
+// error but with the same sign in every element, which sums over many
+// elements carry (the v gradients over 12,800 tokens: 3.3e-6 off instead of
+// 8.5e-7).  So each row of A, and with it the row's results, is negated or
+// not, at random as far as the remainder is concerned, which then does not
+// add up.  For a K-contiguous A the row's first four values decide, by the
+// parity of their bits: a row's results are the same bits wherever it stands,
+// however a sequence is cut into calls.  For a row-contiguous A (a sum over
+// tokens) the row's index decides.
+//
+// The parts are formed once per tile, between the global loads and LDS: the
+// tile's three planes lie in LDS as bf16 [rows][BK + 8], so a fragment of a
+// plane is one 16-byte read.
+//
+// Bound by the matrix units where tiles fill the chip (1.3 PFLOP/s of bf16
+// products, what the library's large bf16 products reach), by the latency of
+// a step (load, split, LDS, six dependent products) where they do not.
+// Against the fp32 instruction on 128 x 128 tiles: 16384 x 3072 x 1024 takes 905 -> 515 us,
+// 3072 x 1024 over 16384 tokens 940 -> 557 us with its split sum, 2048 x 768
+// x 256 24.7 -> 13.1 us.
+//
+// A value whose bf16 rounding is not finite (infinities, NaN, magnitudes
+// above 3.39e38) turns its second part, and so every result it enters, into
+// NaN.  A workgroup that finds a result that is not finite therefore runs
+// its tile again with the fp32 matrix instruction: such results are fp32
+// arithmetic's own.
+#include <algorithm>
+
+#include "sru_gemm_tile.h"
+#include "sru_internal.h"
+
+namespace sru {
+namespace {
+
+// Loads of one operand: 16-byte buffer loads (whole aligned chunks), dword
+// buffer loads (any alignment and extent), or plain loads with 64-bit
+// offsets (panels beyond the buffer offsets' 2 GiB).
+enum LoadMode { kVec16, kDword, kPlain };
+
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int D_>
+struct FCfg {
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, D = D_;
+  static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, WAVES = WAVES_M * WAVES_N;
+  static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+  static constexpr int FM = WM / 32, FN = WN / 32;
+  static constexpr int THREADS = WAVES * 64;
+  // bytes of an LDS row: bf16 plane, fp32 tile (the rerun).  16 bytes of
+  // padding keep the 16 rows of a fragment read on distinct banks.
+  static constexpr int ROWB = 2 * BK + 16, ROWF = 4 * BK + 16;
+  static constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
+  static constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+  static constexpr int LDS = 2 * STAGE;  // two buffers
+  static_assert((BM + BN) * ROWF <= LDS, "the rerun's fp32 tile fits");
+  static_assert(LDS <= 160 * 1024 && BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile");
+};
+
+// Sign bit of row r of a row-contiguous A: the Thue-Morse sequence.
+__device__ __forceinline__ unsigned row_sign(unsigned r) {
+  return (unsigned)__builtin_popcount(r) << 31;
+}
+
+__device__ __forceinline__ float flip(float x, unsigned sign) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) ^ sign);
+}
+
+// Two values' parts, packed per plane.  SIGN: of the values with their signs
+// flipped by sg.
+template <bool SIGN>
+__device__ __forceinline__ void split_pair(float x, float y, unsigned sg, unsigned (&p)[3]) {
+  if constexpr (SIGN) {
+    x = flip(x, sg);
+    y = flip(y, sg);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    p[i] = pack_bf16(x, y);
+    if (i < 2) {
+      x -= __builtin_bit_cast(float, p[i] << 16);
+      y -= __builtin_bit_cast(float, p[i] & 0xFFFF0000u);
+    }
+  }
+}
+
+// Four floats of one chunk (elements e < valid of src + idx).
+template <int MODE>
+__device__ __forceinline__ u32x4 load_chunk(__amdgpu_buffer_rsrc_t rs, const float* src,
+                                            long long idx, unsigned off, int valid) {
+  u32x4 v;
+  if constexpr (MODE == kVec16) {
+    v = buf_load16(rs, valid > 0 ? off : kOOB);
+  } else if constexpr (MODE == kDword) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, e < valid ? off + 4u * e : kOOB, 0, 0);
+  } else {
+    v = load16_elems(src, idx, valid);
+  }
+  return v;
+}
+
+// K-contiguous operand: element (r, k) at src[r*ld + k].  A thread owns
+// chunks of four k of one row.
+template <class C, int R, int MODE>
+struct FLoadKC {
+  static constexpr int CPR = C::BK / 4;
+  static constexpr int PER = R * CPR / C::THREADS;
+  static_assert(R * CPR % C::THREADS == 0, "tile splits evenly over the threads");
+  struct Regs {
+    u32x4 v[PER];
+  };
+  unsigned off[PER];  // bytes from (row r0, the stage's k); rows clamped to the last
+  unsigned sign[PER];  // sign bit of the chunk's row (signs())
+  int r0, rows;
+  long long ld, bytes;
+  const float* src;
+
+  __device__ __forceinline__ void init(const float* s, long long ld_, int r0_, int rows_, int K,
+                                       int tid) {
+    src = s;
+    ld = ld_;
+    r0 = r0_;
+    rows = rows_;
+    bytes = 4 * ((long long)(rows - 1) * ld + K);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      const int r = min(c / CPR, rows - 1 - r0);
+      off[i] = (unsigned)(((long long)r * ld + (c % CPR) * 4) * 4);
+    }
+  }
+  // The rows' signs, for the split and (table) the results.
+  __device__ __forceinline__ void signs(unsigned* table, int K, int tid) {
+    const long long base = 4 * (long long)r0 * ld;
+    const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, bytes);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      const u32x4 v = load_chunk<MODE>(rs, src, (long long)min(r0 + c / CPR, rows - 1) * ld,
+                                       off[i] - (unsigned)(c % CPR) * 16u, K);
+      sign[i] = row_sign(v[0] ^ v[1] ^ v[2] ^ v[3]);
+      if (c % CPR == 0) table[c / CPR] = sign[i];
+    }
+  }
+  __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
+    const long long base = 4 * ((long long)r0 * ld + k0);
+    const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, max(bytes, base));
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      const int k = k0 + (c % CPR) * 4;
+      const long long idx = (long long)min(r0 + c / CPR, rows - 1) * ld + k;
+      g.v[i] = load_chunk<MODE>(rs, src, idx, off[i], kend - k);
+    }
+  }
+  // SIGN: the rows take their signs.
+  template <bool SIGN>
+  __device__ __forceinline__ void store(const Regs& g, unsigned char* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      unsigned char* dst = lds + (c / CPR) * C::ROWB + (c % CPR) * 8;
+      unsigned p[2][3];
+      split_pair<SIGN>(f32_of(g.v[i], 0), f32_of(g.v[i], 1), sign[i], p[0]);
+      split_pair<SIGN>(f32_of(g.v[i], 2), f32_of(g.v[i], 3), sign[i], p[1]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        u32x2 w;
+        w[0] = p[0][q];
+        w[1] = p[1][q];
+        *reinterpret_cast<u32x2*>(dst + q * R * C::ROWB) = w;
+      }
+    }
+  }
+  __device__ __forceinline__ void store_f32(const Regs& g, unsigned char* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      *reinterpret_cast<u32x4*>(lds + (c / CPR) * C::ROWF + (c % CPR) * 16) = g.v[i];
+    }
+  }
+};
+
+// Row-contiguous operand: element (r, k) at src[k*ld + r].  A thread owns KB
+// k-rows of four rows and transposes them on the way into LDS; consecutive
+// threads take consecutive k-blocks of the same rows.
+template <class C, int R, int MODE>
+struct FLoadRC {
+  static constexpr int KB = R * C::BK / 16 >= C::THREADS ? 4 : 2;
+  static constexpr int NKB = C::BK / KB;
+  static constexpr int PER = (R / 4) * NKB / C::THREADS;
+  static_assert((R / 4) * NKB % C::THREADS == 0 && PER > 0, "tile splits evenly over the threads");
+  struct Regs {
+    u32x4 v[PER][KB];
+  };
+  unsigned off[PER];  // bytes from (row r0, the stage's k)
+  unsigned sign[PER];  // sign bit of the block's first row (signs())
+  int r0, rows;
+  long long ld, bytes;
+  const float* src;
+
+  __device__ __forceinline__ void init(const float* s, long long ld_, int r0_, int rows_, int K,
+                                       int tid) {
+    src = s;
+    ld = ld_;
+    r0 = r0_;
+    rows = rows_;
+    bytes = 4 * ((long long)(K - 1) * ld + rows);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      off[i] = (unsigned)(((long long)(c % NKB) * KB * ld + (c / NKB) * 4) * 4);
+    }
+  }
+  __device__ __forceinline__ void signs(unsigned* table, int, int tid) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) sign[i] = row_sign(r0 + (tid + i * C::THREADS) / NKB * 4);
+    if (tid < R) table[tid] = row_sign(r0 + tid);
+  }
+  __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
+    const long long base = 4 * ((long long)k0 * ld + r0);
+    const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, max(bytes, base));
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+      const int r = r0 + (c / NKB) * 4;
+#pragma unroll
+      for (int kk = 0; kk < KB; ++kk) {
+        const int k = k0 + (c % NKB) * KB + kk;
+        g.v[i][kk] = load_chunk<MODE>(rs, src, (long long)k * ld + r,
+                                      off[i] + (unsigned)(kk * ld * 4), k < kend ? rows - r : 0);
+      }
+    }
+  }
+  // SIGN: the rows take their signs.
+  template <bool SIGN>
+  __device__ __forceinline__ void store(const Regs& g, unsigned char* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        unsigned char* dst = lds + ((c / NKB) * 4 + e) * C::ROWB + (c % NKB) * 2 * KB;
+        unsigned p[KB / 2][3];
+#pragma unroll
+        for (int h = 0; h < KB / 2; ++h)
+          split_pair<SIGN>(f32_of(g.v[i][2 * h], e), f32_of(g.v[i][2 * h + 1], e),
+                           sign[i] ^ row_sign(e), p[h]);  // r0 and the block are multiples of 4
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          if constexpr (KB == 4) {
+            u32x2 w;
+            w[0] = p[0][q];
+            w[1] = p[1][q];
+            *reinterpret_cast<u32x2*>(dst + q * R * C::ROWB) = w;
+          } else {
+            *reinterpret_cast<unsigned*>(dst + q * R * C::ROWB) = p[0][q];
+          }
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void store_f32(const Regs& g, unsigned char* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = tid + i * C::THREADS;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk)
+          *reinterpret_cast<float*>(lds + ((c / NKB) * 4 + e) * C::ROWF +
+                                    ((c % NKB) * KB + kk) * 4) = f32_of(g.v[i][kk], e);
+    }
+  }
+};
+
+// Workgroup barrier that waits for this wave's LDS accesses only: the fence
+// of __syncthreads would also drain the loads of the stages ahead.
+__device__ __forceinline__ void lds_only_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) (vmcnt 63, expcnt 7)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <class C, bool A_KC, bool B_KC, int MODE>
+__global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
+  __shared__ unsigned row_signs[C::BM];
+
+  const TileIdx ti = tile_of(g);
+  const int m0 = ti.tm * C::BM;
+  const int n0 = ti.tn * C::BN;
+  const int kbeg = ti.split * g.k_per_split;
+  const int kend = min(g.K, kbeg + g.k_per_split);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int wm0 = (wave / C::WAVES_N) * C::WM;
+  const int wn0 = (wave % C::WAVES_N) * C::WN;
+
+  using LA = std::conditional_t<A_KC, FLoadKC<C, C::BM, MODE>, FLoadRC<C, C::BM, MODE>>;
+  using LB = std::conditional_t<B_KC, FLoadKC<C, C::BN, MODE>, FLoadRC<C, C::BN, MODE>>;
+  LA la;
+  LB lb;
+  la.init(static_cast<const float*>(g.A), g.lda, m0, g.M, g.K, tid);
+  lb.init(static_cast<const float*>(g.B), g.ldb, n0, g.N, g.K, tid);
+
+  // low: a second accumulator for the five small terms in the sums over
+  // tokens where registers allow (one MFMA tile per wave): a slab then rounds
+  // the sum once instead of 6 times.  (Not in the other products, whose
+  // results are the same bits in every tile.)
+  constexpr bool LOW = C::FM * C::FN == 1 && !A_KC;
+  floatx16 acc[C::FM][C::FN], low;
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    if constexpr (LOW) low = acc[0][0];
+  };
+  clear();
+
+  // Pipeline: the loads of stages k + 1 .. k + D are in flight (D register
+  // sets) while the matrix instructions run stage k from one LDS buffer;
+  // stage k + 1 is then split into the other.  Stages past the end load
+  // zeros (out-of-range offsets), so no branch separates the loads.
+  typename LA::Regs ra[C::D];
+  typename LB::Regs rb[C::D];
+  const int nk = (kend - kbeg + C::BK - 1) / C::BK;
+  auto load = [&](int p, int kt) {
+    la.load(ra[p], kbeg + kt * C::BK, kend, tid);
+    lb.load(rb[p], kbeg + kt * C::BK, kend, tid);
+  };
+  auto store = [&](int p, int kt) {
+    unsigned char* s = smem + (kt & 1) * C::STAGE;
+    la.template store<true>(ra[p], s, tid);
+    lb.template store<false>(rb[p], s + 3 * C::A_PLANE, tid);
+  };
+  auto compute = [&](int kt) {
+    const unsigned char* As = smem + (kt & 1) * C::STAGE;
+    const unsigned char* Bs = As + 3 * C::A_PLANE;
+#pragma unroll
+    for (int ks = 0; ks < C::BK; ks += 16) {
+      const int ko = (ks + (lane >> 5) * 8) * 2;
+      bf16x8 af[C::FM][3], bf[C::FN][3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+          af[i][q] = *reinterpret_cast<const bf16x8*>(
+              As + q * C::A_PLANE + (wm0 + i * 32 + (lane & 31)) * C::ROWB + ko);
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+          bf[j][q] = *reinterpret_cast<const bf16x8*>(
+              Bs + q * C::B_PLANE + (wn0 + j * 32 + (lane & 31)) * C::ROWB + ko);
+      }
+      // the small terms first
+      constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < C::FN; ++j) {
+            floatx16& c = LOW && q < 5 ? low : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][PA[q]], bf[j][PB[q]], c, 0, 0, 0);
+          }
+    }
+  };
+
+#pragma unroll
+  for (int p = 0; p < C::D; ++p) load(p, p);
+  la.signs(row_signs, g.K, tid);
+  store(0, 0);
+  lds_only_barrier();
+  for (int k0 = 0; k0 < nk; k0 += C::D) {
+#pragma unroll
+    for (int p = 0; p < C::D; ++p) {
+      const int kt = k0 + p;
+      if (kt < nk) {
+        load(p, kt + C::D);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(kt);
+        store((p + 1) % C::D, kt + 1);
+        lds_only_barrier();
+      }
+    }
+  }
+
+  if constexpr (LOW) acc[0][0] += low;
+#pragma unroll
+  for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const unsigned sg = row_signs[wm0 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j) {
+        const float x = acc[i][j][e];
+        acc[i][j][e] = flip(x, sg);
+      }
+    }
+
+  // Results that are not finite: once more in fp32 (see the top of the file).
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) z = fmaf(acc[i][j][e], 0.f, z);
+  unsigned* flag = reinterpret_cast<unsigned*>(smem);
+  const bool bad = __ballot(!(z == 0.f)) != 0;
+  if (lane == 0) flag[wave] = bad;
+  lds_only_barrier();
+  unsigned any = 0;
+#pragma unroll
+  for (int w = 0; w < C::WAVES; ++w) any |= flag[w];
+  if (__builtin_amdgcn_readfirstlane(any)) {
+    clear();
+    for (int kt = 0; kt < nk; ++kt) {
+      load(0, kt);
+      lds_only_barrier();  // every wave is done with the tile (the flags)
+      la.store_f32(ra[0], smem, tid);
+      lb.store_f32(rb[0], smem + C::BM * C::ROWF, tid);
+      lds_only_barrier();
+      for (int ks = 0; ks < C::BK; ks += 2) {
+        const int ko = (ks + (lane >> 5)) * 4;
+        float af[C::FM], bf[C::FN];
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+          af[i] = *reinterpret_cast<const float*>(smem + (wm0 + i * 32 + (lane & 31)) * C::ROWF +
+                                                  ko);
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j)
+          bf[j] = *reinterpret_cast<const float*>(
+              smem + (C::BM + wn0 + j * 32 + (lane & 31)) * C::ROWF + ko);
+#pragma unroll
+        for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+          for (int j = 0; j < C::FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+  if (g.add_count == 0) write_tile_add<C, 0>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+  else if (g.add_count == 1) write_tile_add<C, 1>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+  else write_tile_add<C, 2>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+}
+
+// Tiles.  Big: 8 waves of 64 x 128, one workgroup per CU; fewest bytes and
+// LDS reads per operation.  Mid: 4 waves of 64 x 64, two workgroups per CU.
+// Small: 4 waves of 32 x 32, two per CU, for products of few tiles.
+using FBig = FCfg<256, 256, 16, 4, 2, 2>;
+using FMid = FCfg<128, 128, 16, 2, 2, 2>;
+using FSmall = FCfg<64, 64, 32, 2, 2, 2>;
+
+// Time of a product in us: per 16 k, one time for a workgroup alone on its CU
+// and one for each of several, and what a workgroup's start and end add; a
+// split adds its partials' traffic and the launch that sums them.  From times
+// measured over K 128 .. 16384, M 128 .. 16384.  16384 x 3072 x 1024 runs at
+// 215 TFLOP/s on Big, 182 on Mid, 129 on Small (the fp32 instruction: 114);
+// 2048 x 768 x 256 takes 35, 18.5 and 12.6 us (24); 128 x 384 x 128 24, 12
+// and 6.1 us (14.3).
+struct TileCost {
+  int bm, bn, bk;
+  double base_alone, alone, base_shared, shared;
+};
+constexpr TileCost kTiles[3] = {{FBig::BM, FBig::BN, FBig::BK, 7.0, 2.35, 7.0, 2.4},
+                                {FMid::BM, FMid::BN, FMid::BK, 4.0, 0.90, 2.0, 0.74},
+                                {FSmall::BM, FSmall::BN, FSmall::BK, 3.0, 0.33, 1.5, 0.25}};
+constexpr double kSumLaunch = 4.0, kBytesPerUs = 4.5e6;
+
+struct Plan {
+  int tile, splits;
+};
+
+// The product over all tokens (row-contiguous A) is split, into chains of at
+// most 2048 terms, and others where the caller gives room for partials
+// (kc_split).  The Big and Mid tiles round 6 times per 16 k, so on few
+// output tiles, where the sum has many short chains anyway, they keep to
+// chains of about 1/380 of the terms times the 128 x 128 tiles; Small rounds
+// once.  The choice depends on the sizes alone, so a workspace sized from it
+// fits whatever the pointers and pitches are.
+//
+// A K-contiguous product is split only where its 128 x 128 tiles fill at most
+// a quarter of the CUs: its other results do not depend on M, so that a
+// sequence cut into calls gives one call's bits.
+Plan plan_f32(const GemmDesc& g) {
+  Plan best{0, 1};
+  double best_cost = -1.0;
+  const int mid_tiles = (int)std::min<long long>(
+      ((g.M + 127LL) / 128) * ((g.N + 127LL) / 128), 1 << 20);
+  for (int t = 0; t < 3; ++t) {
+    const TileCost& c = kTiles[t];
+    const long long tiles = (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
+    const int kt = (g.K + c.bk - 1) / c.bk;
+    int lo = 1, hi = 1;
+    if (!g.a_kc) {
+      lo = (g.K + 2047) / 2048;
+      if (t < 2) lo = std::max(lo, std::min({48, g.K / 128, (384 + mid_tiles - 1) / mid_tiles}));
+    }
+    if (!g.a_kc || (g.kc_split && mid_tiles <= 64)) hi = std::max(lo, std::min(64, kt / 4));
+    // every count up to 6, then steps of a third or less
+    for (int s = lo; s <= hi; s += std::max(1, s / 6)) {
+      const long long per_cu = (tiles * s + 255) / 256;
+      const double steps = (double)((kt + s - 1) / s) * c.bk / 16;
+      double cost = per_cu == 1 ? c.base_alone + steps * c.alone
+                                : per_cu * (c.base_shared + steps * c.shared);
+      if (s > 1) cost += kSumLaunch + (2 * s + 1) * 4.0 * g.M * g.N / kBytesPerUs;
+      if (best_cost < 0 || cost < best_cost) {
+        best = {t, s};
+        best_cost = cost;
+      }
+    }
+  }
+  // the real number of splits, each of whole K steps
+  const int bk = kTiles[best.tile].bk;
+  const int kt = (g.K + bk - 1) / bk;
+  const int per = (kt + best.splits - 1) / best.splits;
+  best.splits = (kt + per - 1) / per;
+  return best;
+}
+
+// 16-byte loads need chunks that are wholly inside or outside the operand;
+// buffer offsets need a panel (a tile's rows, or a stage's k-rows) below
+// 2 GiB.
+LoadMode load_mode(const GemmDesc& g, int bm, int bn, int bk) {
+  auto whole = [](const void* p, long long ld, int extent) {
+    return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0;
+  };
+  auto fits = [&](bool kc, long long ld, int rows) {
+    return 4 * ((kc ? rows : bk) * ld + std::max(rows, bk)) < (long long)kOOB;
+  };
+  if (!fits(g.a_kc, g.lda, bm) || !fits(g.b_kc, g.ldb, bn)) return kPlain;
+  return whole(g.A, g.lda, g.a_kc ? g.K : g.M) && whole(g.B, g.ldb, g.b_kc ? g.K : g.N) ? kVec16
+                                                                                        : kDword;
+}
+
+template <class C, bool A_KC, bool B_KC>
+void launch_f32(const KernelArgs& a, LoadMode mode, hipStream_t st) {
+  const dim3 grid(a.tiles_m * a.tiles_n * a.splits), block(C::THREADS);
+  if (mode == kVec16)
+    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kVec16>), grid, block, 0, st, a);
+  else if (mode == kDword)
+    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kDword>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kPlain>), grid, block, 0, st, a);
+}
+
+template <class C>
+hipError_t launch_f32_layout(const GemmDesc& g, KernelArgs a, hipStream_t st) {
+  const LoadMode mode = load_mode(g, C::BM, C::BN, C::BK);
+  if (g.a_kc && g.b_kc) launch_f32<C, true, true>(a, mode, st);
+  else if (g.a_kc) launch_f32<C, true, false>(a, mode, st);
+  else if (!g.b_kc) launch_f32<C, false, false>(a, mode, st);
+  else return hipErrorInvalidValue;  // (row-contiguous A with K-contiguous B is not used)
+  return hipSuccess;
+}
+}  // namespace
+
+int gemm_f32_splits(const GemmDesc& g) { return plan_f32(g).splits; }
+
+hipError_t gemm_f32_launch(const GemmDesc& g, hipStream_t st) {
+  const Plan p = plan_f32(g);
+  const TileCost& c = kTiles[p.tile];
+  const int kt = (g.K + c.bk - 1) / c.bk;
+  KernelArgs a{};
+  a.A = g.A;
+  a.B = g.B;
+  a.lda = g.lda;
+  a.ldb = g.ldb;
+  a.M = g.M;
+  a.N = g.N;
+  a.K = g.K;
+  a.k_per_split = ((kt + p.splits - 1) / p.splits) * c.bk;
+  a.tiles_m = (g.M + c.bm - 1) / c.bm;
+  a.tiles_n = (g.N + c.bn - 1) / c.bn;
+  a.splits = p.splits;
+  if (p.splits > 1) {
+    a.out = g.partials;
+    a.ldo = g.N;
+    a.split_stride = (long long)g.M * g.N;
+  } else {
+    a.out = g.C;
+    a.ldo = g.ldc;
+    a.add = g.add;
+    a.add_count = g.add_count;
+    a.add_ld = g.add_ld;
+    a.add_off = g.add_off;
+  }
+  timing_before(gemm_label(g), st);
+  const hipError_t e = p.tile == 0   ? launch_f32_layout<FBig>(g, a, st)
+                       : p.tile == 1 ? launch_f32_layout<FMid>(g, a, st)
+                                     : launch_f32_layout<FSmall>(g, a, st);
+  timing_after(st);
+  return e != hipSuccess ? e : hipGetLastError();
+}
+
+}  // namespace sru

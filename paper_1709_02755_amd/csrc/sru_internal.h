@@ -104,6 +104,14 @@ int gemm_splits(const GemmDesc& g);
 bool gemm_is_direct(const GemmDesc& g);
 size_t gemm_partial_bytes(int M, int N, int splits);
 hipError_t gemm_launch(const GemmDesc& g, hipStream_t stream);
+// fp32 products (sru_gemm_f32.hip): the split count, and the product itself
+// without its split sum.
+int gemm_f32_splits(const GemmDesc& g);
+hipError_t gemm_f32_launch(const GemmDesc& g, hipStream_t stream);
+// Name of a product for the measurement hook.
+inline const char* gemm_label(const GemmDesc& g) {
+  return g.label ? g.label : !g.b_kc ? (g.a_kc ? "gemm_nn" : "gemm_tn") : "gemm_nt";
+}
 
 // ------------------------------------------- fused projection + forward scan
 // Inference with bf16 products: U = X Wcat^T and Eq. 1-4 in one kernel; U
