@@ -507,6 +507,7 @@ int sru_forward(const float* X, const float* W, const float* v_f, const float* v
   // weights rounded), so both operands of the product are K-contiguous bf16.
   const void* Wop = W;
   const void* Xop = X;
+  const bool step = fused && s.M <= sru::kStepMaxTokens && L <= sru::kStepMaxLen;
   if (bf16) {
     uint16_t* wb = W_bf16 ? W_bf16 : static_cast<uint16_t*>(workspace);
     if (!w_rounded) {
@@ -517,6 +518,8 @@ int sru_forward(const float* X, const float* W, const float* v_f, const float* v
     Wop = wb;
     if (X_bf16) {
       Xop = X_bf16;
+    } else if (step && aligned16(X)) {
+      Xop = nullptr;  // the kernel rounds X itself (16-byte loads)
     } else {
       uint16_t* xb = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) +
                                                  align_up(2 * (size_t)s.N * (size_t)d_in));
@@ -553,7 +556,8 @@ int sru_forward(const float* X, const float* W, const float* v_f, const float* v
     f.alpha = op.alpha;
     f.reset_new = op.reset_new;
     f.linear = op.linear;
-    return hip_status(sru::proj_scan_forward_launch(f, stream));
+    return hip_status(step ? sru::step_forward_launch(f, stream)
+                           : sru::proj_scan_forward_launch(f, stream));
   }
   sru::GemmDesc g = gemm_desc(SRU_OP_NT, bf16, (int)s.M, (int)s.N, d_in, Xop, d_in, Wop, d_in, U,
                               s.N);

@@ -139,6 +139,12 @@ struct FusedFwdArgs {
   int reset_new, linear;
 };
 hipError_t proj_scan_forward_launch(const FusedFwdArgs& a, hipStream_t stream);
+// The same for few tokens (sru_step.hip): at most kStepMaxTokens, and few
+// enough steps that the serial scan stays short.  Xb may be null: X is then
+// rounded by the kernel.
+constexpr long long kStepMaxTokens = 128;
+constexpr int kStepMaxLen = 8;
+hipError_t step_forward_launch(const FusedFwdArgs& a, hipStream_t stream);
 
 // ----------------------------------------------------------------- scans
 struct ScanShape {

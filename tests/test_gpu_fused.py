@@ -146,3 +146,53 @@ def test_fused_equals_unfused_on_random_cases(case):
     for k in ("H", "c_last"):
         assert torch.equal(got[k], ref[k]), (k, case)
     assert torch.equal(got["H_bf16"].view(torch.int16), ref["H_bf16"].view(torch.int16)), case
+
+
+# few tokens (one wave per 8 units): 1, 2 and 4 row blocks with remainders,
+# K of one chunk, a ragged slab, a partial and several register sets, several
+# (sequence, unit) rounds of the scan, both ends of its range
+FEW = [
+    # (L, B, d_in, d, direction, masked, alpha, reset_new)
+    (1, 1, 8, 64, O.DIR_FWD, False, 1.0, False),
+    (1, 8, 1024, 1024, O.DIR_FWD, False, 1.0, False),
+    (1, 33, 264, 128, O.DIR_BI, False, 1.0, True),
+    (8, 4, 64, 64, O.DIR_REV, True, 1.7, False),
+    (5, 12, 520, 192, O.DIR_FWD, True, 1.0, True),
+    (3, 21, 192, 192, O.DIR_BI, True, float(np.sqrt(3.0)), False),
+    (2, 64, 256, 256, O.DIR_REV, False, 1.0, False),
+    (1, 128, 1000, 64, O.DIR_FWD, True, 1.0, False),
+    (7, 18, 72, 128, O.DIR_BI, True, 1.0, False),
+]
+
+
+@pytest.mark.parametrize("case", FEW)
+@pytest.mark.parametrize("x", ["fp32", "bf16", "unaligned"])
+def test_few_tokens_equal_unfused_bitwise(case, x):
+    L, B, d_in, d, direction, masked, alpha, reset_new = case
+    c = _case(L, B, d_in, d, direction, masked, L + d)
+    gv = dict(highway_scale=alpha, reset_new=reset_new)
+    ref = _run(c, direction, gv, fused=False)
+    X, W = dev(c["X"]), dev(c["W"])
+    if x == "unaligned":
+        buf = torch.empty(X.numel() + 1, device="cuda")
+        buf[1:] = X.reshape(-1)
+        X = buf[1:].view(X.shape)
+    p = [dev(c[k]) for k in ("v_f", "v_r", "b_f", "b_r")]
+    got = sru.forward(X, sru.round_bf16(W), *p, c0=dev(c["c0"]), direction=direction,
+                      mask=dev(c["mask"]), gemm_dtype=O.GEMM_BF16, store_c=False, keep_u=False,
+                      X_bf16=sru.round_bf16(X) if x == "bf16" else None, **gv)
+    torch.cuda.synchronize()
+    assert got["U"] is None
+    for k in ("H", "c_last"):
+        assert torch.equal(got[k], ref[k]), k
+
+
+@pytest.mark.parametrize("L,B,d_in", [(1, 6, 192), (8, 9, 128)])
+def test_few_tokens_linear_matches_oracle(L, B, d_in):
+    c = _case(L, B, d_in, 128, O.DIR_BI, True, 9)
+    got = _run(c, O.DIR_BI, {}, fused=True, linear=True)
+    torch.cuda.synchronize()
+    rf = O.forward(c["X"], c["W"], None, None, c["b_f"], c["b_r"], c["c0"], O.DIR_BI, c["mask"],
+                   O.GEMM_BF16, linear=True)
+    for k in ("H", "c_last"):
+        check(k, got[k], rf[k], TOL_BF16)
