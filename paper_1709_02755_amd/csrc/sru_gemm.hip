@@ -1,27 +1,14 @@
-// bf16 matrix products of the SRU layer on the gfx950 matrix cores (MFMA);
-// the fp32 ones are in sru_gemm_f32.hip.
+// bf16 matrix products of the SRU layer on the gfx950 matrix cores (MFMA),
+// the conversions to bf16 they read, the sums of split products, and the
+// fused projection + scan.  The products whose operands the direct kernel
+// cannot load, and the fp32 ones, are in sru_gemm_staged.hip.
 //
 // The forward projection of Sec. 3.1 (U = X [W; W_f; W_r]^T over all L*B
 // tokens at once) and the two products of the backward pass (dX = dU W and
 // dW = dU^T X) are one kernel template:
 //     C[M,N] = sum_k A(m,k) B(n,k)
 // with each operand either K-contiguous ("KC": row-major [rows, K]) or
-// row-contiguous ("RC": [K, rows]), and stored as fp32 or bf16.  The loader
-// stages a tile into LDS in bf16: bf16 operands are copied, fp32 ones rounded
-// (RNE, v_cvt_pk_bf16_f32); v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
-// LDS always holds a tile K-contiguous per row ([rows][BK + 16 bytes]), so a
-// lane's MFMA fragment is one 16-byte LDS read.  An RC operand is transposed
-// in registers on its way into LDS: a thread owns a block of k-rows x rows,
-// and packs the k-run of each row (the fp32 -> bf16 pack of a (k, k+1) pair
-// does the transposition; bf16 pairs are joined with v_perm_b32).
-//
-// Loads never branch and are never masked after the fact: a chunk past the
-// end of K is loaded from an out-of-range buffer offset (the hardware returns
-// zeros), and a row past the end of the operand is clamped to its last row
-// (that row only feeds outputs the epilogue discards), so the compiler issues
-// every global load of a K step back to back and waits once.
-// Pipelining: two LDS buffers; the global loads of tile k+1 are in flight
-// while the MFMAs consume tile k; one barrier per K step.
+// row-contiguous ("RC": [K, rows]).
 // Work mapping: one workgroup per output tile (and K split).  Workgroups are
 // dispatched round-robin over the 8 XCDs, so the linear tile order is
 // remapped to give each XCD a contiguous run of tiles that share A panels in
@@ -35,161 +22,6 @@
 
 namespace sru {
 namespace {
-
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_>
-struct Cfg {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_;
-  static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
-  static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  static constexpr int FM = WM / 32, FN = WN / 32;
-  static constexpr int THREADS = WAVES_M * WAVES_N * 64;
-  static constexpr int ESZ = 2;                // bytes per LDS element
-  static constexpr int KPACK = 16 / ESZ;       // elements per 16-byte fragment read
-  static constexpr int KSLAB = 2 * KPACK;      // k covered by one fragment pair
-  static constexpr int LDK = BK + KPACK;       // LDS row stride (16 bytes of padding)
-  static constexpr int A_BYTES = BM * LDK * ESZ;
-  static constexpr int B_BYTES = BN * LDK * ESZ;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static_assert(BK % KSLAB == 0, "BK must hold whole fragment pairs");
-  static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile is a grid of 32x32 MFMA tiles");
-};
-
-using CfgBF16 = Cfg<256, 256, 64, 2, 2>;  // 4 waves of 128x128
-
-// ---- loader for a K-contiguous operand: element (r, k) at src[r*ld + k]
-template <class C, int R, class S, bool VEC>
-struct LoaderKC {
-  static constexpr int E = Src<S>::E;
-  static constexpr int CPR = C::BK / E;  // 16-byte chunks per row
-  static constexpr int PER = R * CPR / C::THREADS;
-  static_assert(R * CPR % C::THREADS == 0, "tile must split evenly over the threads");
-  u32x4 v[PER];
-  unsigned base[PER];  // VEC: byte offset of the chunk at k = 0 (rows clamped)
-
-  __device__ __forceinline__ void init(long long ld, int r0, int rows, int tid) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int c = tid + i * C::THREADS;
-        const int r = min(r0 + c / CPR, rows - 1);
-        const int k = (c % CPR) * E;
-        base[i] = (unsigned)(((long long)r * ld + k) * sizeof(S));
-      }
-    }
-  }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, const S* src, long long ld,
-                                       int r0, int rows, int k0, int K, int tid) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-      const int k = k0 + (c % CPR) * E;
-      if constexpr (VEC) {
-        const unsigned off = k < K ? base[i] + (unsigned)(k0 * sizeof(S)) : kOOB;
-        v[i] = buf_load16(rs, off);
-      } else {
-        const int r = r0 + c / CPR;
-        v[i] = load16_elems(src, (long long)r * ld + k, r < rows ? K - k : 0);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(unsigned char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-      const int r = c / CPR;
-      const int k = (c % CPR) * E;
-      unsigned char* dst = lds + (r * C::LDK + k) * C::ESZ;
-      if constexpr (std::is_same<S, float>::value) {
-        u32x2 w;
-        w[0] = pack_bf16(f32_of(v[i], 0), f32_of(v[i], 1));
-        w[1] = pack_bf16(f32_of(v[i], 2), f32_of(v[i], 3));
-        *reinterpret_cast<u32x2*>(dst) = w;
-      } else {
-        *reinterpret_cast<u32x4*>(dst) = v[i];
-      }
-    }
-  }
-};
-
-// ---- loader for a row-contiguous operand: element (r, k) at src[k*ld + r].
-// A thread owns KB k-rows x E rows (one 16-byte chunk per k-row) and writes
-// E LDS rows of KB elements (16 bytes each).  Consecutive threads take
-// consecutive k-blocks of the same rows, so their LDS writes fall in
-// distinct banks.
-template <class C, int R, class S, bool VEC>
-struct LoaderRC {
-  static constexpr int E = Src<S>::E;              // rows per chunk
-  static constexpr int KB = 8;                     // k per LDS write (16 bytes)
-  static constexpr int NKB = C::BK / KB;
-  static constexpr int NMB = (R / E) * NKB;
-  static constexpr int PER = NMB / C::THREADS;
-  static_assert(NMB % C::THREADS == 0, "tile must split evenly over the threads");
-  u32x4 v[PER][KB];
-  unsigned base[PER];  // VEC: byte offset of k-row kb*KB at k0 = 0 (rows clamped)
-
-  __device__ __forceinline__ void init(long long ld, int r0, int rows, int tid) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int c = tid + i * C::THREADS;
-        const int kb = c % NKB;
-        // rows is a multiple of E here, so a clamped chunk stays whole
-        const int r = min(r0 + (c / NKB) * E, rows - E);
-        base[i] = (unsigned)(((long long)kb * KB * ld + r) * sizeof(S));
-      }
-    }
-  }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, const S* src, long long ld,
-                                       int r0, int rows, int k0, int K, int tid) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-      const int kb = c % NKB;
-#pragma unroll
-      for (int kk = 0; kk < KB; ++kk) {
-        const int k = k0 + kb * KB + kk;
-        if constexpr (VEC) {
-          const unsigned off =
-              k < K ? base[i] + (unsigned)(((long long)k0 + kk) * ld * sizeof(S)) : kOOB;
-          v[i][kk] = buf_load16(rs, off);
-        } else {
-          const int r = r0 + (c / NKB) * E;
-          v[i][kk] = load16_elems(src, (long long)k * ld + r, k < K ? rows - r : 0);
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ void store(unsigned char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-      const int kb = c % NKB;
-      const int r = (c / NKB) * E;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        unsigned char* dst = lds + ((r + e) * C::LDK + kb * KB) * C::ESZ;
-        u32x4 w;
-        if constexpr (std::is_same<S, float>::value) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            w[j] = pack_bf16(f32_of(v[i][2 * j], e), f32_of(v[i][2 * j + 1], e));
-        } else {
-          // element e of chunk kk is half (e % 2) of dword e / 2; pair chunks
-          // (2j, 2j+1) into dword j: low half from k = 2j, high from 2j+1.
-          const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            w[j] = __builtin_amdgcn_perm(v[i][2 * j + 1][e >> 1], v[i][2 * j][e >> 1], sel);
-        }
-        *reinterpret_cast<u32x4*>(dst) = w;
-      }
-    }
-  }
-};
-
-template <class C, int R, bool KC, class S, bool VEC>
-using Loader =
-    typename std::conditional<KC, LoaderKC<C, R, S, VEC>, LoaderRC<C, R, S, VEC>>::type;
 
 // Epilogue of the direct kernel, whose MFMAs take the B-operand fragment
 // first and so accumulate the transposed tile: element e of lane l is row
@@ -431,88 +263,6 @@ __device__ __forceinline__ void write_tile_staged(const KernelArgs& g,
       *reinterpret_cast<floatx4*>(out + (mrow + 4 * s) * g.ldo + n0 + wn0 + cc) = v;
     }
   }
-}
-
-template <class C, bool A_KC, bool B_KC, class SA, class SB, bool VEC, int ADD>
-__global__ __launch_bounds__(C::THREADS) void gemm_kernel(KernelArgs g) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * C::STAGE_BYTES];
-
-  const TileIdx ti = tile_of(g);
-  const int split = ti.split;
-  const int m0 = ti.tm * C::BM;
-  const int n0 = ti.tn * C::BN;
-  const int kbeg = split * g.k_per_split;
-  const int kend = min(g.K, kbeg + g.k_per_split);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm0 = (wave / C::WAVES_N) * C::WM;
-  const int wn0 = (wave % C::WAVES_N) * C::WN;
-  const SA* A = static_cast<const SA*>(g.A);
-  const SB* B = static_cast<const SB*>(g.B);
-
-  Loader<C, C::BM, A_KC, SA, VEC> la;
-  Loader<C, C::BN, B_KC, SB, VEC> lb;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, (unsigned)g.a_bytes);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(B, (unsigned)g.b_bytes);
-  la.init(g.lda, m0, g.M, tid);
-  lb.init(g.ldb, n0, g.N, tid);
-
-  floatx16 acc[C::FM][C::FN];
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  la.load(ra, A, g.lda, m0, g.M, kbeg, kend, tid);
-  lb.load(rb, B, g.ldb, n0, g.N, kbeg, kend, tid);
-  la.store(smem, tid);
-  lb.store(smem + C::A_BYTES, tid);
-  __syncthreads();
-
-  int cur = 0;
-  for (int k0 = kbeg; k0 < kend; k0 += C::BK) {
-    const bool next = k0 + C::BK < kend;
-    if (next) {
-      la.load(ra, A, g.lda, m0, g.M, k0 + C::BK, kend, tid);
-      lb.load(rb, B, g.ldb, n0, g.N, k0 + C::BK, kend, tid);
-    }
-    const unsigned char* As = smem + cur * C::STAGE_BYTES;
-    const unsigned char* Bs = As + C::A_BYTES;
-#pragma unroll
-    for (int ks = 0; ks < C::BK; ks += C::KSLAB) {
-      const int koff = ks + (lane >> 5) * C::KPACK;
-      floatx4 af[C::FM], bfr[C::FN];
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i)
-        af[i] = *reinterpret_cast<const floatx4*>(
-            As + ((wm0 + i * 32 + (lane & 31)) * C::LDK + koff) * C::ESZ);
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j)
-        bfr[j] = *reinterpret_cast<const floatx4*>(
-            Bs + ((wn0 + j * 32 + (lane & 31)) * C::LDK + koff) * C::ESZ);
-#pragma unroll
-      for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, af[i]), __builtin_bit_cast(bf16x8, bfr[j]), acc[i][j], 0,
-              0, 0);
-        }
-    }
-    if (next) {
-      unsigned char* nb = smem + (cur ^ 1) * C::STAGE_BYTES;
-      la.store(nb, tid);
-      lb.store(nb + C::A_BYTES, tid);
-    }
-    __syncthreads();
-    cur ^= 1;
-  }
-
-  write_tile_add<C, ADD>(g, acc, m0, n0, wm0, wn0, lane, split);
 }
 
 // ---------------------------------------------------------------------------
@@ -1324,103 +1074,11 @@ __global__ __launch_bounds__(256) void to_bf16_t_tiled_kernel(const S* __restric
   }
 }
 
-template <class C>
-int splits_for(const GemmDesc& g) {
-  const int tiles = ((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
-  // The K = tokens product (TN) is split.  A K-contiguous one is split only
-  // on request and only when its tiles fill at most a quarter of the CUs:
-  // the 32 tiles of the two-layer d = 256 stack's dX (K = 768) take 21 us
-  // split six ways plus 6 us for the split sum, instead of 66 us; at 100-200
-  // tiles the partials' extra pass costs what the split saves.
-  if (g.a_kc && (!g.kc_split || tiles > 64)) return 1;
-  const int kt = (g.K + C::BK - 1) / C::BK;  // K steps
-  int s = (2 * 256 + tiles - 1) / tiles;     // aim for two workgroups per CU
-  s = min(s, max(1, kt / 4));                // at least 4 K steps per split
-  return max(1, min(s, 64));
-}
-
-// Vector (buffer) loads need 16-byte aligned chunks that are either wholly
-// inside or wholly outside the operand, i.e. the contiguous extent (K for KC,
-// the row count for RC) and the leading dimension are multiples of a chunk,
-// and an operand smaller than the out-of-range sentinel.
-template <class S>
+// Direct loads need 16-byte aligned chunks that are either wholly inside or
+// wholly outside the operand, i.e. the contiguous extent (K for KC, the row
+// count for RC) and the leading dimension are multiples of 8 elements.
 bool whole_chunks(const void* p, long long ld, int contiguous_extent) {
-  constexpr int E = Src<S>::E;
-  return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % E == 0 && contiguous_extent % E == 0;
-}
-template <class S>
-bool vec_ok(const void* p, long long ld, int contiguous_extent, long long bytes) {
-  return whole_chunks<S>(p, ld, contiguous_extent) && bytes > 0 && bytes < (long long)kOOB;
-}
-
-template <class C, bool A_KC, bool B_KC, class SA, class SB, bool VEC>
-void launch_staged(const KernelArgs& a, int nwg, hipStream_t st) {
-  if (a.add_count == 2)
-    hipLaunchKernelGGL((gemm_kernel<C, A_KC, B_KC, SA, SB, VEC, 2>), dim3(nwg), dim3(C::THREADS), 0,
-                       st, a);
-  else if (a.add_count == 1)
-    hipLaunchKernelGGL((gemm_kernel<C, A_KC, B_KC, SA, SB, VEC, 1>), dim3(nwg), dim3(C::THREADS), 0,
-                       st, a);
-  else
-    hipLaunchKernelGGL((gemm_kernel<C, A_KC, B_KC, SA, SB, VEC, 0>), dim3(nwg), dim3(C::THREADS), 0,
-                       st, a);
-}
-
-template <class C, bool A_KC, bool B_KC, class SA, class SB>
-hipError_t launch_cfg(const GemmDesc& g, hipStream_t st) {
-  const int splits = splits_for<C>(g);
-  const int kt = (g.K + C::BK - 1) / C::BK;
-  const int kps = ((kt + splits - 1) / splits) * C::BK;
-  KernelArgs a;
-  a.A = g.A;
-  a.B = g.B;
-  a.lda = g.lda;
-  a.ldb = g.ldb;
-  a.M = g.M;
-  a.N = g.N;
-  a.K = g.K;
-  a.k_per_split = kps;
-  a.tiles_m = (g.M + C::BM - 1) / C::BM;
-  a.tiles_n = (g.N + C::BN - 1) / C::BN;
-  // the real number of splits after rounding kps up to whole K steps
-  a.splits = (g.K + kps - 1) / kps;
-  if (a.splits > 1) {
-    a.out = g.partials;
-    a.ldo = g.N;
-    a.split_stride = (long long)g.M * g.N;
-    a.add = nullptr;
-    a.add_count = 0;
-    a.add_ld = a.add_off = 0;
-  } else {
-    a.out = g.C;
-    a.ldo = g.ldc;
-    a.split_stride = 0;
-    a.add = g.add;
-    a.add_count = g.add_count;
-    a.add_ld = g.add_ld;
-    a.add_off = g.add_off;
-  }
-  const int nwg = a.tiles_m * a.tiles_n * a.splits;
-  // operand extents in bytes: rows x ld (KC) or K x ld (RC), last row exact
-  const long long a_bytes =
-      (long long)sizeof(SA) * (A_KC ? (long long)(g.M - 1) * g.lda + g.K
-                                    : (long long)(g.K - 1) * g.lda + g.M);
-  const long long b_bytes =
-      (long long)sizeof(SB) * (B_KC ? (long long)(g.N - 1) * g.ldb + g.K
-                                    : (long long)(g.K - 1) * g.ldb + g.N);
-  const bool vec = vec_ok<SA>(g.A, g.lda, A_KC ? g.K : g.M, a_bytes) &&
-                   vec_ok<SB>(g.B, g.ldb, B_KC ? g.K : g.N, b_bytes);
-  a.a_bytes = vec ? a_bytes : 0;
-  a.b_bytes = vec ? b_bytes : 0;
-  timing_before(gemm_label(g), st);
-  if (vec)
-    launch_staged<C, A_KC, B_KC, SA, SB, true>(a, nwg, st);
-  else
-    launch_staged<C, A_KC, B_KC, SA, SB, false>(a, nwg, st);
-  timing_after(st);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return finish_product(g, a.splits, st);
+  return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 8 == 0 && contiguous_extent % 8 == 0;
 }
 
 // ---- the direct path: plan (shared by workspace sizing and launch) ----
@@ -1456,8 +1114,8 @@ bool direct_ok(const GemmDesc& g) {
     if (kc) return panel_bytes(true, rows, g.K, ld, 0) < (long long)kOOB;
     return split_allowed(g) ? rc_max_k(rows, ld) >= 64 : rc_max_k(rows, ld) >= g.K;
   };
-  return whole_chunks<uint16_t>(g.A, g.lda, g.a_kc ? g.K : g.M) &&
-         whole_chunks<uint16_t>(g.B, g.ldb, g.b_kc ? g.K : g.N) && g.M > 0 && g.N > 0 &&
+  return whole_chunks(g.A, g.lda, g.a_kc ? g.K : g.M) &&
+         whole_chunks(g.B, g.ldb, g.b_kc ? g.K : g.N) && g.M > 0 && g.N > 0 &&
          g.K > 0 && fits(g.a_kc, g.M, g.lda) && fits(g.b_kc, g.N, g.ldb);
 }
 
@@ -1618,44 +1276,13 @@ hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
   return finish_product(g, splits, st);
 }
 
-// Operand-type combinations that are instantiated: fp32 x fp32 for every
-// layout, plus the bf16-operand products of the layer:
-// U = X W^T (fp32 X, bf16 W), dX = dU W (bf16 dU, bf16 W^T, as NT) and
-// dW = dU^T X (bf16 dU, fp32 X).
-template <class C, bool A_KC, bool B_KC>
-hipError_t launch_types(const GemmDesc& g, hipStream_t st) {
-  if (!g.a_bf16 && !g.b_bf16) return launch_cfg<C, A_KC, B_KC, float, float>(g, st);
-  if constexpr (A_KC && B_KC) {
-    if (!g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, float, uint16_t>(g, st);
-    if (g.a_bf16 && g.b_bf16) return launch_cfg<C, true, true, uint16_t, uint16_t>(g, st);
-  }
-  if constexpr (!A_KC && !B_KC) {
-    if (g.a_bf16 && !g.b_bf16) return launch_cfg<C, false, false, uint16_t, float>(g, st);
-    if (g.a_bf16 && g.b_bf16) return launch_cfg<C, false, false, uint16_t, uint16_t>(g, st);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <class C>
-hipError_t launch_layout(const GemmDesc& g, hipStream_t st) {
-  if (g.a_kc && g.b_kc) return launch_types<C, true, true>(g, st);
-  if (g.a_kc && !g.b_kc) return launch_types<C, true, false>(g, st);
-  if (!g.a_kc && !g.b_kc) return launch_types<C, false, false>(g, st);
-  return hipErrorInvalidValue;  // (row-contiguous A with K-contiguous B is not used)
-}
-
 }  // namespace
 
 bool gemm_is_direct(const GemmDesc& g) { return direct_ok(g); }
 
 int gemm_splits(const GemmDesc& g) {
   if (direct_ok(g)) return direct_splits(g);
-  if (!g.bf16) return gemm_f32_splits(g);
-  const int s = splits_for<CfgBF16>(g);
-  const int bk = CfgBF16::BK;
-  const int kt = (g.K + bk - 1) / bk;
-  const int kps = ((kt + s - 1) / s) * bk;
-  return (g.K + kps - 1) / kps;
+  return gemm_staged_splits(g);
 }
 
 SplitSum gemm_split_sum(const GemmDesc& g) { return split_sum_of(g, gemm_splits(g)); }
@@ -1680,9 +1307,8 @@ hipError_t gemm_launch(const GemmDesc& g, hipStream_t st) {
     return launch_direct_cfg<CfgDirectKC, false, false>(g, st);
   }
   if (g.Cb) return hipErrorInvalidValue;  // a bf16 result needs the direct path
-  if (g.bf16) return launch_layout<CfgBF16>(g, st);
-  if (hipError_t e = gemm_f32_launch(g, st)) return e;
-  return finish_product(g, gemm_f32_splits(g), st);
+  if (hipError_t e = gemm_staged_launch(g, st)) return e;
+  return finish_product(g, gemm_staged_splits(g), st);
 }
 
 template <class S>

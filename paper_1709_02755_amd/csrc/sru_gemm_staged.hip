@@ -1,6 +1,11 @@
-// fp32 matrix products on the bf16 matrix units (gfx950).
+// Matrix products staged through registers (gfx950): the fp32 products, and
+// the bf16 ones whose operands the direct kernel cannot load (rows that are
+// not whole aligned 16-byte chunks, operands still in fp32).
 //
-//     C[M,N] = sum_k A(m,k) B(n,k),  A, B, C fp32
+//     C[M,N] = sum_k A(m,k) B(n,k),  fp32 result
+//
+// Both use the bf16 matrix instruction; bf16 products round their operands
+// (RNE) into one plane, fp32 products split theirs into three.
 //
 // The fp32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at a sixteenth
 // of the bf16 one's rate.  An fp32 value is exactly the sum of three bf16
@@ -49,14 +54,15 @@
 namespace sru {
 namespace {
 
-// Loads of one operand: 16-byte buffer loads (whole aligned chunks), dword
-// buffer loads (any alignment and extent), or plain loads with 64-bit
-// offsets (panels beyond the buffer offsets' 2 GiB).
-enum LoadMode { kVec16, kDword, kPlain };
+// Loads of the operands: buffer loads of whole aligned chunks of four
+// elements, buffer loads of single elements (any alignment and extent), or
+// plain loads with 64-bit offsets (panels beyond the buffer offsets' 2 GiB).
+enum LoadMode { kChunk, kSingle, kPlain };
 
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int D_>
+// NP: bf16 planes per operand (3: fp32 products, 1: bf16 products).
+template <int NP_, int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int D_>
 struct FCfg {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, D = D_;
+  static constexpr int NP = NP_, BM = BM_, BN = BN_, BK = BK_, D = D_;
   static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, WAVES = WAVES_M * WAVES_N;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int FM = WM / 32, FN = WN / 32;
@@ -65,9 +71,9 @@ struct FCfg {
   // padding keep the 16 rows of a fragment read on distinct banks.
   static constexpr int ROWB = 2 * BK + 16, ROWF = 4 * BK + 16;
   static constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
-  static constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+  static constexpr int STAGE = NP * (A_PLANE + B_PLANE);
   static constexpr int LDS = 2 * STAGE;  // two buffers
-  static_assert((BM + BN) * ROWF <= LDS, "the rerun's fp32 tile fits");
+  static_assert(NP == 1 || (BM + BN) * ROWF <= LDS, "the rerun's fp32 tile fits");
   static_assert(LDS <= 160 * 1024 && BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile");
 };
 
@@ -82,43 +88,70 @@ __device__ __forceinline__ float flip(float x, unsigned sign) {
 
 // Two values' parts, packed per plane.  SIGN: of the values with their signs
 // flipped by sg.
-template <bool SIGN>
-__device__ __forceinline__ void split_pair(float x, float y, unsigned sg, unsigned (&p)[3]) {
+template <bool SIGN, int NP>
+__device__ __forceinline__ void split_pair(float x, float y, unsigned sg, unsigned (&p)[NP]) {
   if constexpr (SIGN) {
     x = flip(x, sg);
     y = flip(y, sg);
   }
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < NP; ++i) {
     p[i] = pack_bf16(x, y);
-    if (i < 2) {
+    if (i < NP - 1) {
       x -= __builtin_bit_cast(float, p[i] << 16);
       y -= __builtin_bit_cast(float, p[i] & 0xFFFF0000u);
     }
   }
 }
 
-// Four floats of one chunk (elements e < valid of src + idx).
-template <int MODE>
-__device__ __forceinline__ u32x4 load_chunk(__amdgpu_buffer_rsrc_t rs, const float* src,
+// The elements of one chunk of four (element e is valid when e < valid), as
+// loaded: fp32 one per register; bf16 two per register (kChunk) or one.
+template <int MODE, class S>
+__device__ __forceinline__ u32x4 load_chunk(__amdgpu_buffer_rsrc_t rs, const S* src,
                                             long long idx, unsigned off, int valid) {
   u32x4 v;
-  if constexpr (MODE == kVec16) {
+  if constexpr (MODE == kChunk && sizeof(S) == 4) {
     v = buf_load16(rs, valid > 0 ? off : kOOB);
-  } else if constexpr (MODE == kDword) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      v[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, e < valid ? off + 4u * e : kOOB, 0, 0);
+  } else if constexpr (MODE == kChunk) {
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, valid > 0 ? off : kOOB, 0, 0);
+    v[0] = w[0];
+    v[1] = w[1];
   } else {
-    v = load16_elems(src, idx, valid);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool ok = e < valid;
+      if constexpr (MODE == kPlain)
+        v[e] = ok ? __builtin_bit_cast(
+                        std::conditional_t<sizeof(S) == 4, unsigned, uint16_t>, src[ok ? idx + e : 0])
+                  : 0u;
+      else if constexpr (sizeof(S) == 4)
+        v[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, ok ? off + 4u * e : kOOB, 0, 0);
+      else
+        v[e] = __builtin_amdgcn_raw_buffer_load_b16(rs, ok ? off + 2u * e : kOOB, 0, 0);
+    }
   }
   return v;
 }
 
+// Element e of a loaded chunk as fp32.
+template <int MODE, class S>
+__device__ __forceinline__ float elem(const u32x4& v, int e) {
+  if constexpr (sizeof(S) == 4) {
+    return f32_of(v, e);
+  } else if constexpr (MODE == kChunk) {
+    const unsigned w = v[e >> 1];
+    return __builtin_bit_cast(float, e & 1 ? w & 0xFFFF0000u : w << 16);
+  } else {
+    const unsigned w = v[e];
+    return __builtin_bit_cast(float, w << 16);
+  }
+}
+
 // K-contiguous operand: element (r, k) at src[r*ld + k].  A thread owns
 // chunks of four k of one row.
-template <class C, int R, int MODE>
+template <class C, int R, int MODE, class S>
 struct FLoadKC {
+  static constexpr int ES = sizeof(S);
   static constexpr int CPR = C::BK / 4;
   static constexpr int PER = R * CPR / C::THREADS;
   static_assert(R * CPR % C::THREADS == 0, "tile splits evenly over the threads");
@@ -129,44 +162,44 @@ struct FLoadKC {
   unsigned sign[PER];  // sign bit of the chunk's row (signs())
   int r0, rows;
   long long ld, bytes;
-  const float* src;
+  const S* src;
 
-  __device__ __forceinline__ void init(const float* s, long long ld_, int r0_, int rows_, int K,
+  __device__ __forceinline__ void init(const S* s, long long ld_, int r0_, int rows_, int K,
                                        int tid) {
     src = s;
     ld = ld_;
     r0 = r0_;
     rows = rows_;
-    bytes = 4 * ((long long)(rows - 1) * ld + K);
+    bytes = ES * ((long long)(rows - 1) * ld + K);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * C::THREADS;
       const int r = min(c / CPR, rows - 1 - r0);
-      off[i] = (unsigned)(((long long)r * ld + (c % CPR) * 4) * 4);
+      off[i] = (unsigned)(((long long)r * ld + (c % CPR) * 4) * ES);
     }
   }
   // The rows' signs, for the split and (table) the results.
   __device__ __forceinline__ void signs(unsigned* table, int K, int tid) {
-    const long long base = 4 * (long long)r0 * ld;
+    const long long base = ES * (long long)r0 * ld;
     const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, bytes);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * C::THREADS;
-      const u32x4 v = load_chunk<MODE>(rs, src, (long long)min(r0 + c / CPR, rows - 1) * ld,
-                                       off[i] - (unsigned)(c % CPR) * 16u, K);
+      const u32x4 v = load_chunk<MODE, S>(rs, src, (long long)min(r0 + c / CPR, rows - 1) * ld,
+                                       off[i] - (unsigned)((c % CPR) * 4 * ES), K);
       sign[i] = row_sign(v[0] ^ v[1] ^ v[2] ^ v[3]);
       if (c % CPR == 0) table[c / CPR] = sign[i];
     }
   }
   __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
-    const long long base = 4 * ((long long)r0 * ld + k0);
+    const long long base = ES * ((long long)r0 * ld + k0);
     const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, max(bytes, base));
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * C::THREADS;
       const int k = k0 + (c % CPR) * 4;
       const long long idx = (long long)min(r0 + c / CPR, rows - 1) * ld + k;
-      g.v[i] = load_chunk<MODE>(rs, src, idx, off[i], kend - k);
+      g.v[i] = load_chunk<MODE, S>(rs, src, idx, off[i], kend - k);
     }
   }
   // SIGN: the rows take their signs.
@@ -176,11 +209,13 @@ struct FLoadKC {
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * C::THREADS;
       unsigned char* dst = lds + (c / CPR) * C::ROWB + (c % CPR) * 8;
-      unsigned p[2][3];
-      split_pair<SIGN>(f32_of(g.v[i], 0), f32_of(g.v[i], 1), sign[i], p[0]);
-      split_pair<SIGN>(f32_of(g.v[i], 2), f32_of(g.v[i], 3), sign[i], p[1]);
+      unsigned p[2][C::NP];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
+      for (int h = 0; h < 2; ++h)
+        split_pair<SIGN>(elem<MODE, S>(g.v[i], 2 * h), elem<MODE, S>(g.v[i], 2 * h + 1),
+                         SIGN ? sign[i] : 0u, p[h]);
+#pragma unroll
+      for (int q = 0; q < C::NP; ++q) {
         u32x2 w;
         w[0] = p[0][q];
         w[1] = p[1][q];
@@ -200,8 +235,9 @@ struct FLoadKC {
 // Row-contiguous operand: element (r, k) at src[k*ld + r].  A thread owns KB
 // k-rows of four rows and transposes them on the way into LDS; consecutive
 // threads take consecutive k-blocks of the same rows.
-template <class C, int R, int MODE>
+template <class C, int R, int MODE, class S>
 struct FLoadRC {
+  static constexpr int ES = sizeof(S);
   static constexpr int KB = R * C::BK / 16 >= C::THREADS ? 4 : 2;
   static constexpr int NKB = C::BK / KB;
   static constexpr int PER = (R / 4) * NKB / C::THREADS;
@@ -213,19 +249,19 @@ struct FLoadRC {
   unsigned sign[PER];  // sign bit of the block's first row (signs())
   int r0, rows;
   long long ld, bytes;
-  const float* src;
+  const S* src;
 
-  __device__ __forceinline__ void init(const float* s, long long ld_, int r0_, int rows_, int K,
+  __device__ __forceinline__ void init(const S* s, long long ld_, int r0_, int rows_, int K,
                                        int tid) {
     src = s;
     ld = ld_;
     r0 = r0_;
     rows = rows_;
-    bytes = 4 * ((long long)(K - 1) * ld + rows);
+    bytes = ES * ((long long)(K - 1) * ld + rows);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * C::THREADS;
-      off[i] = (unsigned)(((long long)(c % NKB) * KB * ld + (c / NKB) * 4) * 4);
+      off[i] = (unsigned)(((long long)(c % NKB) * KB * ld + (c / NKB) * 4) * ES);
     }
   }
   __device__ __forceinline__ void signs(unsigned* table, int, int tid) {
@@ -234,7 +270,7 @@ struct FLoadRC {
     if (tid < R) table[tid] = row_sign(r0 + tid);
   }
   __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
-    const long long base = 4 * ((long long)k0 * ld + r0);
+    const long long base = ES * ((long long)k0 * ld + r0);
     const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, max(bytes, base));
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -243,8 +279,8 @@ struct FLoadRC {
 #pragma unroll
       for (int kk = 0; kk < KB; ++kk) {
         const int k = k0 + (c % NKB) * KB + kk;
-        g.v[i][kk] = load_chunk<MODE>(rs, src, (long long)k * ld + r,
-                                      off[i] + (unsigned)(kk * ld * 4), k < kend ? rows - r : 0);
+        g.v[i][kk] = load_chunk<MODE, S>(rs, src, (long long)k * ld + r,
+                                      off[i] + (unsigned)(kk * ld * ES), k < kend ? rows - r : 0);
       }
     }
   }
@@ -257,13 +293,13 @@ struct FLoadRC {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         unsigned char* dst = lds + ((c / NKB) * 4 + e) * C::ROWB + (c % NKB) * 2 * KB;
-        unsigned p[KB / 2][3];
+        unsigned p[KB / 2][C::NP];
 #pragma unroll
-        for (int h = 0; h < KB / 2; ++h)
-          split_pair<SIGN>(f32_of(g.v[i][2 * h], e), f32_of(g.v[i][2 * h + 1], e),
-                           sign[i] ^ row_sign(e), p[h]);  // r0 and the block are multiples of 4
+        for (int h = 0; h < KB / 2; ++h)  // (r0 and the block are multiples of 4)
+          split_pair<SIGN>(elem<MODE, S>(g.v[i][2 * h], e), elem<MODE, S>(g.v[i][2 * h + 1], e),
+                           SIGN ? sign[i] ^ row_sign(e) : 0u, p[h]);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
+        for (int q = 0; q < C::NP; ++q) {
           if constexpr (KB == 4) {
             u32x2 w;
             w[0] = p[0][q];
@@ -285,7 +321,7 @@ struct FLoadRC {
 #pragma unroll
         for (int kk = 0; kk < KB; ++kk)
           *reinterpret_cast<float*>(lds + ((c / NKB) * 4 + e) * C::ROWF +
-                                    ((c % NKB) * KB + kk) * 4) = f32_of(g.v[i][kk], e);
+                                    ((c % NKB) * KB + kk) * 4) = elem<MODE, S>(g.v[i][kk], e);
     }
   }
 };
@@ -300,10 +336,10 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("" ::: "memory");
 }
 
-template <class C, bool A_KC, bool B_KC, int MODE>
-__global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
+template <class C, bool A_KC, bool B_KC, int MODE, class S>
+__global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
-  __shared__ unsigned row_signs[C::BM];
+  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
 
   const TileIdx ti = tile_of(g);
   const int m0 = ti.tm * C::BM;
@@ -316,18 +352,19 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
   const int wm0 = (wave / C::WAVES_N) * C::WM;
   const int wn0 = (wave % C::WAVES_N) * C::WN;
 
-  using LA = std::conditional_t<A_KC, FLoadKC<C, C::BM, MODE>, FLoadRC<C, C::BM, MODE>>;
-  using LB = std::conditional_t<B_KC, FLoadKC<C, C::BN, MODE>, FLoadRC<C, C::BN, MODE>>;
+  using LA = std::conditional_t<A_KC, FLoadKC<C, C::BM, MODE, S>, FLoadRC<C, C::BM, MODE, S>>;
+  using LB = std::conditional_t<B_KC, FLoadKC<C, C::BN, MODE, S>, FLoadRC<C, C::BN, MODE, S>>;
   LA la;
   LB lb;
-  la.init(static_cast<const float*>(g.A), g.lda, m0, g.M, g.K, tid);
-  lb.init(static_cast<const float*>(g.B), g.ldb, n0, g.N, g.K, tid);
+  la.init(static_cast<const S*>(g.A), g.lda, m0, g.M, g.K, tid);
+  lb.init(static_cast<const S*>(g.B), g.ldb, n0, g.N, g.K, tid);
 
   // low: a second accumulator for the five small terms in the sums over
   // tokens where registers allow (one MFMA tile per wave): a slab then rounds
   // the sum once instead of 6 times.  (Not in the other products, whose
   // results are the same bits in every tile.)
-  constexpr bool LOW = C::FM * C::FN == 1 && !A_KC;
+  constexpr bool F32 = C::NP == 3;
+  constexpr bool LOW = F32 && C::FM * C::FN == 1 && !A_KC;
   floatx16 acc[C::FM][C::FN], low;
   auto clear = [&]() {
 #pragma unroll
@@ -353,18 +390,18 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
   };
   auto store = [&](int p, int kt) {
     unsigned char* s = smem + (kt & 1) * C::STAGE;
-    la.template store<true>(ra[p], s, tid);
-    lb.template store<false>(rb[p], s + 3 * C::A_PLANE, tid);
+    la.template store<F32>(ra[p], s, tid);
+    lb.template store<false>(rb[p], s + C::NP * C::A_PLANE, tid);
   };
   auto compute = [&](int kt) {
     const unsigned char* As = smem + (kt & 1) * C::STAGE;
-    const unsigned char* Bs = As + 3 * C::A_PLANE;
+    const unsigned char* Bs = As + C::NP * C::A_PLANE;
 #pragma unroll
     for (int ks = 0; ks < C::BK; ks += 16) {
       const int ko = (ks + (lane >> 5) * 8) * 2;
-      bf16x8 af[C::FM][3], bf[C::FN][3];
+      bf16x8 af[C::FM][C::NP], bf[C::FN][C::NP];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
+      for (int q = 0; q < C::NP; ++q) {
 #pragma unroll
         for (int i = 0; i < C::FM; ++i)
           af[i][q] = *reinterpret_cast<const bf16x8*>(
@@ -377,7 +414,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
       // the small terms first
       constexpr int PA[6] = {0, 2, 1, 0, 1, 0}, PB[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int q = F32 ? 0 : 5; q < 6; ++q)
 #pragma unroll
         for (int i = 0; i < C::FM; ++i)
 #pragma unroll
@@ -390,7 +427,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
 
 #pragma unroll
   for (int p = 0; p < C::D; ++p) load(p, p);
-  la.signs(row_signs, g.K, tid);
+  if constexpr (F32) la.signs(row_signs, g.K, tid);
   store(0, 0);
   lds_only_barrier();
   for (int k0 = 0; k0 < nk; k0 += C::D) {
@@ -407,58 +444,60 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
     }
   }
 
-  if constexpr (LOW) acc[0][0] += low;
+  if constexpr (F32) {
+    if constexpr (LOW) acc[0][0] += low;
 #pragma unroll
-  for (int i = 0; i < C::FM; ++i)
+    for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const unsigned sg = row_signs[wm0 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
+      for (int e = 0; e < 16; ++e) {
+        const unsigned sg = row_signs[wm0 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
 #pragma unroll
-      for (int j = 0; j < C::FN; ++j) {
-        const float x = acc[i][j][e];
-        acc[i][j][e] = flip(x, sg);
+        for (int j = 0; j < C::FN; ++j) {
+          const float x = acc[i][j][e];
+          acc[i][j][e] = flip(x, sg);
+        }
       }
-    }
 
-  // Results that are not finite: once more in fp32 (see the top of the file).
-  float z = 0.f;
+    // Results that are not finite: once more in fp32 (see the top of the file).
+    float z = 0.f;
 #pragma unroll
-  for (int i = 0; i < C::FM; ++i)
+    for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-    for (int j = 0; j < C::FN; ++j)
+      for (int j = 0; j < C::FN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) z = fmaf(acc[i][j][e], 0.f, z);
-  unsigned* flag = reinterpret_cast<unsigned*>(smem);
-  const bool bad = __ballot(!(z == 0.f)) != 0;
-  if (lane == 0) flag[wave] = bad;
-  lds_only_barrier();
-  unsigned any = 0;
+        for (int e = 0; e < 16; ++e) z = fmaf(acc[i][j][e], 0.f, z);
+    unsigned* flag = reinterpret_cast<unsigned*>(smem);
+    const bool bad = __ballot(!(z == 0.f)) != 0;
+    if (lane == 0) flag[wave] = bad;
+    lds_only_barrier();
+    unsigned any = 0;
 #pragma unroll
-  for (int w = 0; w < C::WAVES; ++w) any |= flag[w];
-  if (__builtin_amdgcn_readfirstlane(any)) {
-    clear();
-    for (int kt = 0; kt < nk; ++kt) {
-      load(0, kt);
-      lds_only_barrier();  // every wave is done with the tile (the flags)
-      la.store_f32(ra[0], smem, tid);
-      lb.store_f32(rb[0], smem + C::BM * C::ROWF, tid);
-      lds_only_barrier();
-      for (int ks = 0; ks < C::BK; ks += 2) {
-        const int ko = (ks + (lane >> 5)) * 4;
-        float af[C::FM], bf[C::FN];
+    for (int w = 0; w < C::WAVES; ++w) any |= flag[w];
+    if (__builtin_amdgcn_readfirstlane(any)) {
+      clear();
+      for (int kt = 0; kt < nk; ++kt) {
+        load(0, kt);
+        lds_only_barrier();  // every wave is done with the tile (the flags)
+        la.store_f32(ra[0], smem, tid);
+        lb.store_f32(rb[0], smem + C::BM * C::ROWF, tid);
+        lds_only_barrier();
+        for (int ks = 0; ks < C::BK; ks += 2) {
+          const int ko = (ks + (lane >> 5)) * 4;
+          float af[C::FM], bf[C::FN];
 #pragma unroll
-        for (int i = 0; i < C::FM; ++i)
-          af[i] = *reinterpret_cast<const float*>(smem + (wm0 + i * 32 + (lane & 31)) * C::ROWF +
-                                                  ko);
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j)
-          bf[j] = *reinterpret_cast<const float*>(
-              smem + (C::BM + wn0 + j * 32 + (lane & 31)) * C::ROWF + ko);
-#pragma unroll
-        for (int i = 0; i < C::FM; ++i)
+          for (int i = 0; i < C::FM; ++i)
+            af[i] = *reinterpret_cast<const float*>(smem + (wm0 + i * 32 + (lane & 31)) * C::ROWF +
+                                                    ko);
 #pragma unroll
           for (int j = 0; j < C::FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+            bf[j] = *reinterpret_cast<const float*>(
+                smem + (C::BM + wn0 + j * 32 + (lane & 31)) * C::ROWF + ko);
+#pragma unroll
+          for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+        }
       }
     }
   }
@@ -470,33 +509,43 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_f32_kernel(KernelArgs g) {
 // Tiles.  Big: 8 waves of 64 x 128, one workgroup per CU; fewest bytes and
 // LDS reads per operation.  Mid: 4 waves of 64 x 64, two workgroups per CU.
 // Small: 4 waves of 32 x 32, two per CU, for products of few tiles.
-using FBig = FCfg<256, 256, 16, 4, 2, 2>;
-using FMid = FCfg<128, 128, 16, 2, 2, 2>;
-using FSmall = FCfg<64, 64, 32, 2, 2, 2>;
+template <int NP>
+using FBig = FCfg<NP, 256, 256, NP == 3 ? 16 : 32, 4, 2, 2>;
+template <int NP>
+using FMid = FCfg<NP, 128, 128, NP == 3 ? 16 : 32, 2, 2, 2>;
+template <int NP>
+using FSmall = FCfg<NP, 64, 64, NP == 3 ? 32 : 64, 2, 2, 2>;
 
 // Time of a product in us: per 16 k, one time for a workgroup alone on its CU
 // and one for each of several, and what a workgroup's start and end add; a
 // split adds its partials' traffic and the launch that sums them.  From times
-// measured over K 128 .. 16384, M 128 .. 16384.  16384 x 3072 x 1024 runs at
-// 215 TFLOP/s on Big, 182 on Mid, 129 on Small (the fp32 instruction: 114);
-// 2048 x 768 x 256 takes 35, 18.5 and 12.6 us (24); 128 x 384 x 128 24, 12
-// and 6.1 us (14.3).
+// measured over K 128 .. 16384, M 128 .. 16384.  fp32: 16384 x 3072 x 1024
+// runs at 215 TFLOP/s on Big, 182 on Mid, 129 on Small (the fp32
+// instruction: 114); 2048 x 768 x 256 takes 35, 18.5 and 12.6 us (24); 128 x
+// 384 x 128 24, 12 and 6.1 us (14.3).  bf16 (before: one 256 x 256 tile,
+// element-wise loads where rows were no whole 16-byte chunks): 1001 x 1600 x
+// 300 9.1 us (31.5 with fp32 operands, 92 with bf16 ones), 12800 x 900 x 300
+// 27 (35), 4000 x 771 x 257 21 (80), 16384 x 3072 x 1024 143 (208).
 struct TileCost {
   int bm, bn, bk;
   double base_alone, alone, base_shared, shared;
 };
-constexpr TileCost kTiles[3] = {{FBig::BM, FBig::BN, FBig::BK, 7.0, 2.35, 7.0, 2.4},
-                                {FMid::BM, FMid::BN, FMid::BK, 4.0, 0.90, 2.0, 0.74},
-                                {FSmall::BM, FSmall::BN, FSmall::BK, 3.0, 0.33, 1.5, 0.25}};
+constexpr TileCost kTilesF32[3] = {{256, 256, FBig<3>::BK, 7.0, 2.35, 7.0, 2.4},
+                                   {128, 128, FMid<3>::BK, 4.0, 0.90, 2.0, 0.74},
+                                   {64, 64, FSmall<3>::BK, 3.0, 0.33, 1.5, 0.25}};
+constexpr TileCost kTilesBf16[3] = {{256, 256, FBig<1>::BK, 7.0, 0.80, 7.0, 0.80},
+                                    {128, 128, FMid<1>::BK, 4.0, 0.30, 2.0, 0.25},
+                                    {64, 64, FSmall<1>::BK, 3.0, 0.15, 1.5, 0.10}};
+const TileCost& tile_cost(const GemmDesc& g, int t) { return (g.bf16 ? kTilesBf16 : kTilesF32)[t]; }
 constexpr double kSumLaunch = 4.0, kBytesPerUs = 4.5e6;
 
 struct Plan {
   int tile, splits;
 };
 
-// The product over all tokens (row-contiguous A) is split, into chains of at
-// most 2048 terms, and others where the caller gives room for partials
-// (kc_split).  The Big and Mid tiles round 6 times per 16 k, so on few
+// The product over all tokens (row-contiguous A) is split, for fp32 into
+// chains of at most 2048 terms, and others where the caller gives room for partials
+// (kc_split).  The fp32 Big and Mid tiles round 6 times per 16 k, so on few
 // output tiles, where the sum has many short chains anyway, they keep to
 // chains of about 1/380 of the terms times the 128 x 128 tiles; Small rounds
 // once.  The choice depends on the sizes alone, so a workspace sized from it
@@ -505,17 +554,17 @@ struct Plan {
 // A K-contiguous product is split only where its 128 x 128 tiles fill at most
 // a quarter of the CUs: its other results do not depend on M, so that a
 // sequence cut into calls gives one call's bits.
-Plan plan_f32(const GemmDesc& g) {
+Plan plan_staged(const GemmDesc& g) {
   Plan best{0, 1};
   double best_cost = -1.0;
   const int mid_tiles = (int)std::min<long long>(
       ((g.M + 127LL) / 128) * ((g.N + 127LL) / 128), 1 << 20);
   for (int t = 0; t < 3; ++t) {
-    const TileCost& c = kTiles[t];
+    const TileCost& c = tile_cost(g, t);
     const long long tiles = (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
     const int kt = (g.K + c.bk - 1) / c.bk;
     int lo = 1, hi = 1;
-    if (!g.a_kc) {
+    if (!g.a_kc && !g.bf16) {
       lo = (g.K + 2047) / 2048;
       if (t < 2) lo = std::max(lo, std::min({48, g.K / 128, (384 + mid_tiles - 1) / mid_tiles}));
     }
@@ -534,55 +583,75 @@ Plan plan_f32(const GemmDesc& g) {
     }
   }
   // the real number of splits, each of whole K steps
-  const int bk = kTiles[best.tile].bk;
+  const int bk = tile_cost(g, best.tile).bk;
   const int kt = (g.K + bk - 1) / bk;
   const int per = (kt + best.splits - 1) / best.splits;
   best.splits = (kt + per - 1) / per;
   return best;
 }
 
-// 16-byte loads need chunks that are wholly inside or outside the operand;
-// buffer offsets need a panel (a tile's rows, or a stage's k-rows) below
-// 2 GiB.
+// Chunk loads need chunks that are wholly inside or outside the operand and
+// aligned; buffer offsets need a panel (a tile's rows, or a stage's k-rows)
+// below 2 GiB.
 LoadMode load_mode(const GemmDesc& g, int bm, int bn, int bk) {
-  auto whole = [](const void* p, long long ld, int extent) {
-    return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 4 == 0 && extent % 4 == 0;
+  const long long es = g.a_bf16 ? 2 : 4;
+  auto whole = [&](const void* p, long long ld, int extent) {
+    return reinterpret_cast<uintptr_t>(p) % (4 * es) == 0 && ld % 4 == 0 && extent % 4 == 0;
   };
   auto fits = [&](bool kc, long long ld, int rows) {
-    return 4 * ((kc ? rows : bk) * ld + std::max(rows, bk)) < (long long)kOOB;
+    return es * ((kc ? rows : bk) * ld + std::max(rows, bk)) < (long long)kOOB;
   };
   if (!fits(g.a_kc, g.lda, bm) || !fits(g.b_kc, g.ldb, bn)) return kPlain;
-  return whole(g.A, g.lda, g.a_kc ? g.K : g.M) && whole(g.B, g.ldb, g.b_kc ? g.K : g.N) ? kVec16
-                                                                                        : kDword;
+  return whole(g.A, g.lda, g.a_kc ? g.K : g.M) && whole(g.B, g.ldb, g.b_kc ? g.K : g.N) ? kChunk
+                                                                                        : kSingle;
 }
 
-template <class C, bool A_KC, bool B_KC>
-void launch_f32(const KernelArgs& a, LoadMode mode, hipStream_t st) {
+template <class C, bool A_KC, bool B_KC, class S>
+hipError_t launch_staged(const GemmDesc& g, const KernelArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles_m * a.tiles_n * a.splits), block(C::THREADS);
-  if (mode == kVec16)
-    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kVec16>), grid, block, 0, st, a);
-  else if (mode == kDword)
-    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kDword>), grid, block, 0, st, a);
+  const LoadMode mode = load_mode(g, C::BM, C::BN, C::BK);
+  if (mode == kChunk)
+    hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kChunk, S>), grid, block, 0, st, a);
+  else if (mode == kSingle)
+    hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kSingle, S>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((gemm_f32_kernel<C, A_KC, B_KC, kPlain>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kPlain, S>), grid, block, 0, st, a);
+  return hipGetLastError();
 }
 
+// The operand types and layouts that occur: fp32 operands in every layout in
+// both precisions; bf16 operands as the layer's products read them (U = X
+// W^T and dX = dU (W^T)^T K-contiguous, dW = dU^T X row-contiguous).
 template <class C>
-hipError_t launch_f32_layout(const GemmDesc& g, KernelArgs a, hipStream_t st) {
-  const LoadMode mode = load_mode(g, C::BM, C::BN, C::BK);
-  if (g.a_kc && g.b_kc) launch_f32<C, true, true>(a, mode, st);
-  else if (g.a_kc) launch_f32<C, true, false>(a, mode, st);
-  else if (!g.b_kc) launch_f32<C, false, false>(a, mode, st);
-  else return hipErrorInvalidValue;  // (row-contiguous A with K-contiguous B is not used)
-  return hipSuccess;
+hipError_t launch_layout(const GemmDesc& g, const KernelArgs& a, hipStream_t st) {
+  if (g.a_bf16 != g.b_bf16 || (!g.a_kc && g.b_kc)) return hipErrorInvalidValue;
+  if constexpr (C::NP == 1) {
+    if (g.a_bf16) {
+      if (g.b_kc) return launch_staged<C, true, true, uint16_t>(g, a, st);
+      if (!g.a_kc) return launch_staged<C, false, false, uint16_t>(g, a, st);
+      return hipErrorInvalidValue;
+    }
+  }
+  if (g.a_bf16) return hipErrorInvalidValue;
+  if (g.b_kc) return launch_staged<C, true, true, float>(g, a, st);
+  if (g.a_kc) return launch_staged<C, true, false, float>(g, a, st);
+  return launch_staged<C, false, false, float>(g, a, st);
 }
+
+template <int NP>
+hipError_t launch_tile(int tile, const GemmDesc& g, const KernelArgs& a, hipStream_t st) {
+  return tile == 0   ? launch_layout<FBig<NP>>(g, a, st)
+         : tile == 1 ? launch_layout<FMid<NP>>(g, a, st)
+                     : launch_layout<FSmall<NP>>(g, a, st);
+}
+
 }  // namespace
 
-int gemm_f32_splits(const GemmDesc& g) { return plan_f32(g).splits; }
+int gemm_staged_splits(const GemmDesc& g) { return plan_staged(g).splits; }
 
-hipError_t gemm_f32_launch(const GemmDesc& g, hipStream_t st) {
-  const Plan p = plan_f32(g);
-  const TileCost& c = kTiles[p.tile];
+hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
+  const Plan p = plan_staged(g);
+  const TileCost& c = tile_cost(g, p.tile);
   const int kt = (g.K + c.bk - 1) / c.bk;
   KernelArgs a{};
   a.A = g.A;
@@ -609,11 +678,9 @@ hipError_t gemm_f32_launch(const GemmDesc& g, hipStream_t st) {
     a.add_off = g.add_off;
   }
   timing_before(gemm_label(g), st);
-  const hipError_t e = p.tile == 0   ? launch_f32_layout<FBig>(g, a, st)
-                       : p.tile == 1 ? launch_f32_layout<FMid>(g, a, st)
-                                     : launch_f32_layout<FSmall>(g, a, st);
+  const hipError_t e = g.bf16 ? launch_tile<1>(p.tile, g, a, st) : launch_tile<3>(p.tile, g, a, st);
   timing_after(st);
-  return e != hipSuccess ? e : hipGetLastError();
+  return e;
 }
 
 }  // namespace sru

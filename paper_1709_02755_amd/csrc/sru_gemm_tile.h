@@ -17,11 +17,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-// Source element types: fp32, or bf16 carried as raw 16-bit patterns.
-template <class S> struct Src;
-template <> struct Src<float> { static constexpr int E = 4; };     // elements per 16 bytes
-template <> struct Src<uint16_t> { static constexpr int E = 8; };
-
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   bf16x2 v;
   v[0] = (__bf16)lo;  // RNE (v_cvt_pk_bf16_f32)
@@ -52,21 +47,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const void* p, long
 
 __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-}
-
-// Element-wise variant for unaligned or ragged operands: element e is valid
-// when e < valid.
-template <class S>
-__device__ __forceinline__ u32x4 load16_elems(const S* src, long long idx, int valid) {
-  constexpr int E = Src<S>::E;
-  S tmp[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool ok = e < valid;
-    const S x = src[ok ? idx + e : 0];
-    tmp[e] = ok ? x : S(0);
-  }
-  return __builtin_bit_cast(u32x4, tmp);
 }
 
 // Element e of a 16-byte chunk as fp32.  The element is copied to a scalar

@@ -104,10 +104,10 @@ int gemm_splits(const GemmDesc& g);
 bool gemm_is_direct(const GemmDesc& g);
 size_t gemm_partial_bytes(int M, int N, int splits);
 hipError_t gemm_launch(const GemmDesc& g, hipStream_t stream);
-// fp32 products (sru_gemm_f32.hip): the split count, and the product itself
-// without its split sum.
-int gemm_f32_splits(const GemmDesc& g);
-hipError_t gemm_f32_launch(const GemmDesc& g, hipStream_t stream);
+// The products staged through registers (sru_gemm_staged.hip): the split
+// count, and the product itself without its split sum.
+int gemm_staged_splits(const GemmDesc& g);
+hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t stream);
 // Name of a product for the measurement hook.
 inline const char* gemm_label(const GemmDesc& g) {
   return g.label ? g.label : !g.b_kc ? (g.a_kc ? "gemm_nn" : "gemm_tn") : "gemm_nt";
