@@ -92,6 +92,8 @@ def _options(highway_scale=1.0, reset_new=False, linear=False):
 def lib():
     """Load libsru.so (building it first only if it has never been built)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -121,19 +123,38 @@ def _check(status: int, what: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else _P(t.data_ptr())
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current device's current stream, without building a Stream object
+    return _P(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _on_gpu(t):
     return t.is_cuda
 
 
+_Tensor, _F32, _BF16 = torch.Tensor, torch.float32, torch.bfloat16
+
+
+def _fits(t, shape, dtype, device):
+    """Whether _req would accept t, in one expression and with no message: a
+    small layer's call is bound by the host (L 32, B 4, d 128: 22 us of
+    checks and launches for 10 us of kernels).  Anything unusual is False and
+    left to _req."""
+    return (t.__class__ is _Tensor and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous() and (t.is_cuda or _on_gpu(t)) and t.device == device)
+
+
+def _fits_opt(t, shape, dtype, device):
+    return t is None or _fits(t, shape, dtype, device)
+
+
 def _req(t, name, shape, dtype=torch.float32, optional=False, device=None):
     """A GPU tensor of this shape and dtype, contiguous, on `device` (if given)."""
+    if t.__class__ is _Tensor and _fits(t, shape, dtype, t.device if device is None else device):
+        return
     if t is None:
         if optional:
             return
@@ -167,7 +188,8 @@ def _ws(ws, need, device):
         if not need:
             return None, 0
         ws = workspace(need, device)
-    _req(ws, "ws", (ws.numel(),), dtype=torch.uint8, device=device)
+    else:
+        _req(ws, "ws", (ws.numel(),), dtype=torch.uint8, device=device)
     return ws, ws.numel() * ws.element_size()
 
 
@@ -178,6 +200,21 @@ def dims(X, W):
 
 
 def _check_params(X, W, v_f, v_r, b_f, b_r, c0, direction, mask, gemm_dtype=GEMM_FP32):
+    if X.__class__ is _Tensor and W.__class__ is _Tensor and X.dim() == 3 and W.dim() == 4:
+        L, B, d_in = X.shape
+        ndir, k, d, _ = W.shape
+        dv = X.device
+        vec, state = (ndir, d), (B, ndir * d)
+        if (ndir == (2 if direction == DIR_BI else 1) and k == (3 if d_in == d else 4)
+                and _fits(X, X.shape, _F32, dv)
+                and _fits(W, (ndir, k, d, d_in),
+                          _BF16 if gemm_dtype == GEMM_BF16 and W.dtype is _BF16 else _F32, dv)
+                and _fits_opt(v_f, vec, _F32, dv) and _fits_opt(v_r, vec, _F32, dv)
+                and _fits(b_f, vec, _F32, dv) and _fits(b_r, vec, _F32, dv)
+                and _fits_opt(c0, state, _F32, dv)
+                and _fits_opt(mask, (L, B), torch.uint8, dv)):
+            return L, B, d_in, d, ndir, k
+    # one by one, for the message
     for n, t, nd in (("X", X, 3), ("W", W, 4)):
         if not isinstance(t, torch.Tensor) or t.dim() != nd:
             raise ValueError(f"{n} must be a {nd}-d tensor")
@@ -248,15 +285,16 @@ def forward(X, W, v_f, v_r, b_f, b_r, c0=None, direction=DIR_FWD, mask=None,
     if out is None:
         no_u = not keep_u and not store_c and fused_available(L, B, d_in, d, direction,
                                                                 gemm_dtype)
-        out = dict(U=None if no_u else torch.empty((L, B, ndir, k, d), device=dv),
-                   H=torch.empty((L, B, ndir * d), device=dv),
-                   C=torch.empty((L, B, ndir * d), device=dv) if store_c else None,
-                   c_last=torch.empty((B, ndir * d), device=dv))
-    f32, b16 = torch.float32, torch.bfloat16
-    _req_out(out, dict(U=((L, B, ndir, k, d), f32, False), H=((L, B, ndir * d), f32, True),
-                       C=((L, B, ndir * d), f32, False), c_last=((B, ndir * d), f32, False),
-                       W_bf16=(tuple(W.shape), b16, False),
-                       H_bf16=((L, B, ndir * d), b16, False)), dv)
+        out = dict(U=None if no_u else X.new_empty((L, B, ndir, k, d)),
+                   H=X.new_empty((L, B, ndir * d)),
+                   C=X.new_empty((L, B, ndir * d)) if store_c else None,
+                   c_last=X.new_empty((B, ndir * d)))
+    else:
+        f32, b16 = torch.float32, torch.bfloat16
+        _req_out(out, dict(U=((L, B, ndir, k, d), f32, False), H=((L, B, ndir * d), f32, True),
+                           C=((L, B, ndir * d), f32, False), c_last=((B, ndir * d), f32, False),
+                           W_bf16=(tuple(W.shape), b16, False),
+                           H_bf16=((L, B, ndir * d), b16, False)), dv)
     Wf, Wb = _weights(W, out.get("W_bf16"))
     ws, nbytes = _ws(ws, forward_workspace_bytes(L, B, d_in, d, direction, gemm_dtype), dv)
     st = lib().sru_forward(_ptr(X), _ptr(Wf), _ptr(v_f), _ptr(v_r), _ptr(b_f), _ptr(b_r),
