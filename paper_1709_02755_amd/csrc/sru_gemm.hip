@@ -197,38 +197,9 @@ __device__ __forceinline__ void write_tile_staged(const KernelArgs& g,
                                                   const floatx16 (&acc)[C::FM][C::FN],
                                                   unsigned char* smem, int m0, int n0, int wm0,
                                                   int wn0, int lane, int wave, int split) {
-  static_assert(C::WN == 64 || C::WN == 96, "staged rows of 64 or 96 columns");
+  static_assert(C::WN == 64, "staged rows of 64 columns");
   float* out = g.out + (long long)split * g.split_stride;
   const int cl = 4 * (lane >> 5);
-  if constexpr (C::WN == 96) {
-    // 96-column wave blocks: rows of 24 16-byte chunks (pitch 100 floats, 4
-    // past a multiple of 32 banks as for 64 columns), read back as 12 passes
-    // of 64 consecutive chunks of the 32-row group (runs of 384 bytes)
-    static_assert(ADD == 0, "the 96-column tiles serve products without an addend");
-    constexpr int P = 100, CPR = 24;
-    static_assert(C::WAVES * 32 * P * 4 <= C::LDS, "staging fits the operand stages");
-    float* blk = reinterpret_cast<float*>(smem) + wave * 32 * P;
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          floatx4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
-          *reinterpret_cast<floatx4*>(blk + (lane & 31) * P + j * 32 + 8 * q + cl) = v;
-        }
-#pragma unroll
-      for (int s = 0; s < 32 * CPR / 64; ++s) {
-        const int ch = s * 64 + lane, r = ch / CPR, col = 4 * (ch % CPR);
-        const long long mrow = m0 + wm0 + i * 32 + r;
-        *reinterpret_cast<floatx4*>(out + mrow * g.ldo + n0 + wn0 + col) =
-            *reinterpret_cast<const floatx4*>(blk + r * P + col);
-      }
-    }
-    return;
-  }
   static_assert(C::WAVES * 32 * kStagePitch * 4 <= C::LDS, "staging fits the operand stages");
   float* blk = reinterpret_cast<float*>(smem) + wave * 32 * kStagePitch;
   const int rr = lane >> 4, cc = 4 * (lane & 15);  // read-back: rows rr + 4 s, columns cc..cc+3
@@ -316,17 +287,24 @@ struct DCfg {
   static constexpr int OCC = LDS <= 80 * 1024 ? 2 : 1;  // workgroups per CU
   static_assert(SA == STAGES || SA == STAGES + 1, "A ring depth");
   static_assert(BK == 32 || BK == 64, "k per stage");
-  static_assert((WM == 128 && WN == 64) || (WM == 64 && (WN == 96 || WN == 128)), "wave block");
+  static_assert((WM == 128 && WN == 64) || (WM == 64 && (WN == 64 || WN == 96 || WN == 128)),
+                "wave block");
   static_assert(A_BPW * 1024 * WAVES == A_OPB && B_BPW * 1024 * WAVES == B_OPB,
                 "whole 1 KiB load blocks per wave");
   static_assert(LDS <= 160 * 1024 && IPS * (SA - 1) < 64, "LDS and vmcnt");
 };
-using DirectTall = DCfg<256, 128, 32, 2, 2, 3>;  // 4 waves, 2 workgroups per CU
-using DirectWide = DCfg<256, 256, 32, 2, 4, 4>;  // 8 waves, 1 workgroup per CU
-using DirectLine = DCfg<256, 256, 64, 2, 4, 2>;  // 8 waves, whole-line loads
-using DirectLineA3 = DCfg<256, 256, 64, 2, 4, 2, 3>;  // the same, A two K steps ahead (160 KiB)
-using DirectNarrow = DCfg<256, 128, 64, 2, 2, 2, 3>;  // 4 waves, whole-line loads, half the columns
-using DirectN96 = DCfg<256, 96, 64, 4, 1, 2, 3>;  // 4 waves of 64 x 96
+// Big tiles: 8 waves of 128 x 64, one workgroup per CU.  K-contiguous
+// operands load A two K steps ahead (160 KiB).
+using CfgBigKC = DCfg<256, 256, 64, 2, 4, 2, 3>;
+using CfgBigRC = DCfg<256, 256, 64, 2, 4, 2>;
+// Mid tiles, for products of few big ones: 4 waves of 64 x 64, two
+// workgroups per CU, so that one's loads and epilogue run beside the other's
+// MFMAs.  Against 256 x 128 tiles of 4 waves (one wave per SIMD), us:
+// 2048 x 3072 x 1024 24.1 -> 20.3, 2048 x 1024 x 3072 in two splits 30.4 ->
+// 21.2, 16384 x 512 x 1024 25.7 -> 23.3, 512 x 3072 x 1024 19.7 -> 12.6; 3072
+// x 1024 over 2048 tokens 25.0 (big, 5 splits) -> 21.4 (2 splits).
+using CfgMidKC = DCfg<128, 128, 64, 2, 2, 2, 3>;
+using CfgMidRC = DCfg<128, 128, 64, 2, 2, 2>;
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_t;
@@ -1106,10 +1084,9 @@ bool split_allowed(const GemmDesc& g) { return !g.Cb && (!g.a_kc || g.kc_split);
 // panels fit the 32-bit offsets: a K-contiguous operand's 256 rows, a
 // row-contiguous one's whole K when the product is not split, else one
 // 64-k stage (the split count then keeps each split's panel in range, see
-// direct_splits_cfg).  Layouts: both K-contiguous, both row-contiguous, or A
-// K-contiguous with B row-contiguous.
+// plan_direct).  Layouts: both K-contiguous or both row-contiguous.
 bool direct_ok(const GemmDesc& g) {
-  if (!g.bf16 || !g.a_bf16 || !g.b_bf16 || (!g.a_kc && g.b_kc)) return false;
+  if (!g.bf16 || !g.a_bf16 || !g.b_bf16 || g.a_kc != g.b_kc) return false;
   auto fits = [&](bool kc, int rows, long long ld) {
     if (kc) return panel_bytes(true, rows, g.K, ld, 0) < (long long)kOOB;
     return split_allowed(g) ? rc_max_k(rows, ld) >= 64 : rc_max_k(rows, ld) >= g.K;
@@ -1119,116 +1096,76 @@ bool direct_ok(const GemmDesc& g) {
          g.K > 0 && fits(g.a_kc, g.M, g.lda) && fits(g.b_kc, g.N, g.ldb);
 }
 
-// Split count for the direct path: the K = tokens product (row-contiguous
-// operands) is cut over K so that the CUs share the work evenly, and so is a
-// K-contiguous product whose caller asks for it (kc_split: dX of a small
-// batch, whose few tiles would leave most CUs idle).  A bf16 result (Cb) is
-// never split.  The count
-// minimises a cost in K steps: the rounds of workgroups over the CUs times
-// the K steps of a split, plus the split partials' HBM traffic ((s + 1)
-// fp32 outputs written and read) at kSplitBytesPerStep, the bytes HBM moves
-// in the time of one K step (a 64 KiB stage takes ~2 us per CU; ~6 TB/s).
-// At least 8 K steps per split.  E.g. 48 tiles x 256 steps: 5 splits (240
-// workgroups, 52 steps); 192 tiles x 256 steps: 4 splits (768 workgroups,
-// three rounds of 64 steps) rather than 192 workgroups of 256 steps.
-constexpr double kSplitBytesPerStep = 11.0 * (1 << 20);
-template <class C>
-int direct_splits_cfg(const GemmDesc& g) {
-  static_assert(C::BK == 64, "rc_max_k counts 64-k stages");
-  if (!split_allowed(g)) return 1;
-  const long long tiles = (long long)((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
-  const int kt = (g.K + C::BK - 1) / C::BK;
-  const long long slots = C::OCC * 256LL;  // workgroups the CUs run at once
-  const double out_bytes = 4.0 * g.M * g.N;
+// Time in us of wg workgroups of st K steps (64 k) each, from times measured
+// over 32 to 3072 workgroups and 8 to 128 steps.  Big: rounds of one per CU,
+// whose steps slow down as the chip fills (shared caches and clock).  Mid: two
+// per CU run at half speed each; an odd one left over runs alone.
+double direct_cost(bool mid, bool rc, long long wg, double st) {
+  const long long n = (wg + 255) / 256;
+  if (!mid) return n * (8.0 + st * (1.2 + 0.5 * std::min(1.0, wg / 256.0)));
+  return 3.0 + (n / 2) * 2 * (1.4 + 0.51 * st) + (n % 2) * (2.0 + (rc ? 0.85 : 0.62) * st);
+}
+
+// Tile and split count of a direct product: the least modelled time.  The
+// K = tokens product (row-contiguous operands) may be cut over K, and so may
+// a K-contiguous product whose caller asks for it (kc_split: dX of a small
+// batch, whose few tiles would leave most CUs idle), with at least 6 K steps
+// per split; the split sum reads the partials at about 6.5 TB/s.  A bf16
+// result (Cb) is never split.  E.g. 3072 x 1024 over 16384 tokens: big tiles
+// in 5 splits (240 workgroups of 52 steps, 101 us and 12 for the sum); over
+// 2048: mid tiles in 2 (21 and 6 us; big ones in 5: 25 and 12).
+struct DirectPlan {
+  bool mid;
+  int splits;
+};
+DirectPlan plan_direct(const GemmDesc& g) {
+  const bool rc = !g.a_kc;
+  const int kt = (g.K + 63) / 64;
   // fewest splits whose row-contiguous panels fit (direct_ok: one stage does)
   long long kmax = kt;
-  if (!g.a_kc) kmax = min(kmax, rc_max_k(g.M, g.lda) / C::BK);
-  if (!g.b_kc) kmax = min(kmax, rc_max_k(g.N, g.ldb) / C::BK);
-  kmax = max(kmax, 1LL);
-  const int s_min = (int)((kt + kmax - 1) / kmax);
-  int best = s_min;
-  double best_cost = 0.0;
-  for (int s = s_min; s <= max(s_min, kt / 8); ++s) {
-    const long long rounds = (tiles * s + slots - 1) / slots;
-    const int steps = (kt + s - 1) / s;
-    const double cost =
-        (double)(rounds * steps) + (s > 1 ? (s + 1) * out_bytes / kSplitBytesPerStep : 0.0);
-    if (s == s_min || cost < best_cost) {
-      best = s;
-      best_cost = cost;
+  if (rc) kmax = std::max(1LL, std::min({kmax, rc_max_k(g.M, g.lda) / 64, rc_max_k(g.N, g.ldb) / 64}));
+  const int s_min = split_allowed(g) ? (int)((kt + kmax - 1) / kmax) : 1;
+  const int s_max = split_allowed(g) ? std::max(s_min, kt / 6) : 1;
+  DirectPlan best{false, s_min};
+  double best_cost = -1.0;
+  for (int m = 0; m < 2; ++m) {
+    const int b = m ? 128 : 256;
+    const long long tiles = (long long)((g.M + b - 1) / b) * ((g.N + b - 1) / b);
+    // every count up to 8, then steps of a quarter or less
+    for (int s = s_min; s <= s_max; s += std::max(1, s / 8)) {
+      const int steps = (kt + s - 1) / s;
+      double cost = direct_cost(m, rc, tiles * s, steps);
+      if (s > 1) cost += 2.0 + (s + 1) * 4.0 * g.M * g.N / 6.5e6;
+      if (best_cost < 0 || cost < best_cost) {
+        best = {m != 0, s};
+        best_cost = cost;
+      }
     }
   }
-  const int kps = ((kt + best - 1) / best) * C::BK;
-  return (g.K + kps - 1) / kps;
-}
-
-using CfgDirect = DirectLine;
-// Both operands K-contiguous (U = X W^T, dX = dU W on W^T): the A operand's
-// ring gets the third slot, 5-6 % faster on the 256 x 256 tiles of these
-// products; the row-contiguous dW product runs slower with it.
-using CfgDirectKC = DirectLineA3;
-// K-contiguous products whose 256 x 256 tiles would leave CUs idle (N of a
-// few hundred, e.g. the rank-dp products of the projection trick, or few
-// tokens, e.g. dX of one GPU's share of a batch) use 256 x 128 tiles: twice
-// the workgroups, and fewer K splits where a split is planned (dX of 2,048
-// tokens at d = 1024: 4 splits of 64 tiles instead of 6 of 32, a third less
-// partial traffic).
-using CfgNarrow = DirectNarrow;
-
-bool use_narrow(const GemmDesc& g) {
-  if (!g.a_kc || !g.b_kc) return false;
-  const long long tiles = (long long)((g.M + CfgDirect::BM - 1) / CfgDirect::BM) *
-                          ((g.N + CfgDirect::BN - 1) / CfgDirect::BN);
-  return tiles < 256;
-}
-
-using CfgN96 = DirectN96;
-// A product that is never split and has no addend (U = X W^T), whose
-// 256 x 128 tiles still leave CUs idle and whose N is a whole number of
-// 96-column tiles that fill more of them, runs on 256 x 96 tiles (one GPU's
-// share of a batch: 2,048 tokens x 3,072 columns make 256 such tiles against
-// 192 of 256 x 128).
-bool use_n96(const GemmDesc& g) {
-  if (!use_narrow(g) || split_allowed(g) || g.add_count != 0 || g.N % CfgN96::BN != 0)
-    return false;
-  const long long tm = (g.M + CfgN96::BM - 1) / CfgN96::BM;
-  const long long t128 = tm * ((g.N + CfgNarrow::BN - 1) / CfgNarrow::BN);
-  const long long t96 = tm * (g.N / CfgN96::BN);
-  return t128 < 256 && t96 > t128 && t96 <= 256;
-}
-
-// The split count of the configuration gemm_launch runs g on.
-int direct_splits(const GemmDesc& g) {
-  if (!g.a_kc || !g.b_kc) return direct_splits_cfg<CfgDirect>(g);
-  if (use_n96(g)) return 1;
-  if (use_narrow(g)) return direct_splits_cfg<CfgNarrow>(g);
-  return direct_splits_cfg<CfgDirectKC>(g);
+  const int per = (kt + best.splits - 1) / best.splits;
+  best.splits = (kt + per - 1) / per;  // the real number, each of whole K steps
+  return best;
 }
 
 // Explicit instantiations: the host pass did not emit the launch stubs of
 // every specialisation referenced through launch_direct_cfg.
 #define SRU_DIRECT_INST(CFG, ADD, ARC, BRC, OB) \
   template __global__ void gemm_direct_kernel<CFG, ADD, ARC, BRC, OB>(KernelArgs);
-SRU_DIRECT_INST(CfgDirectKC, 0, false, false, false)
-SRU_DIRECT_INST(CfgDirectKC, 1, false, false, false)
-SRU_DIRECT_INST(CfgDirectKC, 2, false, false, false)
-SRU_DIRECT_INST(CfgDirect, 0, true, true, false)
-SRU_DIRECT_INST(CfgDirect, 1, true, true, false)
-SRU_DIRECT_INST(CfgDirect, 2, true, true, false)
-SRU_DIRECT_INST(CfgDirect, 0, false, true, false)
-SRU_DIRECT_INST(CfgDirect, 1, false, true, false)
-SRU_DIRECT_INST(CfgDirect, 2, false, true, false)
-SRU_DIRECT_INST(CfgDirectKC, 0, false, false, true)
-SRU_DIRECT_INST(CfgNarrow, 0, false, false, false)
-SRU_DIRECT_INST(CfgN96, 0, false, false, false)
-SRU_DIRECT_INST(CfgNarrow, 1, false, false, false)
-SRU_DIRECT_INST(CfgNarrow, 2, false, false, false)
-SRU_DIRECT_INST(CfgNarrow, 0, false, false, true)
+SRU_DIRECT_INST(CfgBigKC, 0, false, false, false)
+SRU_DIRECT_INST(CfgBigKC, 1, false, false, false)
+SRU_DIRECT_INST(CfgBigKC, 2, false, false, false)
+SRU_DIRECT_INST(CfgBigKC, 0, false, false, true)
+SRU_DIRECT_INST(CfgMidKC, 0, false, false, false)
+SRU_DIRECT_INST(CfgMidKC, 1, false, false, false)
+SRU_DIRECT_INST(CfgMidKC, 2, false, false, false)
+SRU_DIRECT_INST(CfgMidKC, 0, false, false, true)
+SRU_DIRECT_INST(CfgBigRC, 0, true, true, false)
+SRU_DIRECT_INST(CfgMidRC, 0, true, true, false)
 #undef SRU_DIRECT_INST
 
-template <class C, bool A_RC, bool B_RC, bool OB = false>
-hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
-  const int splits = direct_splits_cfg<C>(g);
+template <class C, bool RC, bool OB = false>
+hipError_t launch_direct_cfg(const GemmDesc& g, int splits, hipStream_t st) {
+  static_assert(C::BK == 64, "the plan counts 64-k steps");
   const int kt = (g.K + C::BK - 1) / C::BK;
   const int kps = ((kt + splits - 1) / splits) * C::BK;
   KernelArgs a{};
@@ -1265,11 +1202,11 @@ hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
               (!OB || (a.ldob % 4 == 0 && ((uintptr_t)a.outb & 7) == 0));
   const int nwg = a.tiles_m * a.tiles_n * splits;
   timing_before(gemm_label(g), st);
-  if constexpr (OB) launch_direct<C, 0, A_RC, B_RC, true>(a, nwg, st);
-  else if constexpr (C::WN == 96) launch_direct<C, 0, A_RC, B_RC>(a, nwg, st);  // no addend
-  else if (a.add_count == 2) launch_direct<C, 2, A_RC, B_RC>(a, nwg, st);
-  else if (a.add_count == 1) launch_direct<C, 1, A_RC, B_RC>(a, nwg, st);
-  else launch_direct<C, 0, A_RC, B_RC>(a, nwg, st);
+  if constexpr (OB) launch_direct<C, 0, RC, RC, true>(a, nwg, st);
+  else if constexpr (RC) launch_direct<C, 0, RC, RC>(a, nwg, st);  // no addend
+  else if (a.add_count == 2) launch_direct<C, 2, RC, RC>(a, nwg, st);
+  else if (a.add_count == 1) launch_direct<C, 1, RC, RC>(a, nwg, st);
+  else launch_direct<C, 0, RC, RC>(a, nwg, st);
   timing_after(st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1281,7 +1218,7 @@ hipError_t launch_direct_cfg(const GemmDesc& g, hipStream_t st) {
 bool gemm_is_direct(const GemmDesc& g) { return direct_ok(g); }
 
 int gemm_splits(const GemmDesc& g) {
-  if (direct_ok(g)) return direct_splits(g);
+  if (direct_ok(g)) return plan_direct(g).splits;
   return gemm_staged_splits(g);
 }
 
@@ -1294,17 +1231,20 @@ size_t gemm_partial_bytes(int M, int N, int splits) {
 hipError_t gemm_launch(const GemmDesc& g, hipStream_t st) {
   if ((g.a_bf16 || g.b_bf16) && !g.bf16) return hipErrorInvalidValue;
   if (direct_ok(g)) {
+    const DirectPlan p = plan_direct(g);
     if (g.Cb) {
       // bf16 result: K-contiguous operands, no addend (never split)
-      if (!g.a_kc || !g.b_kc || g.add_count != 0) return hipErrorInvalidValue;
-      return use_narrow(g) ? launch_direct_cfg<CfgNarrow, false, false, true>(g, st)
-                           : launch_direct_cfg<CfgDirectKC, false, false, true>(g, st);
+      if (!g.a_kc || g.add_count != 0) return hipErrorInvalidValue;
+      return p.mid ? launch_direct_cfg<CfgMidKC, false, true>(g, 1, st)
+                   : launch_direct_cfg<CfgBigKC, false, true>(g, 1, st);
     }
-    if (!g.a_kc) return launch_direct_cfg<CfgDirect, true, true>(g, st);
-    if (!g.b_kc) return launch_direct_cfg<CfgDirect, false, true>(g, st);
-    if (use_n96(g)) return launch_direct_cfg<CfgN96, false, false>(g, st);
-    if (use_narrow(g)) return launch_direct_cfg<CfgNarrow, false, false>(g, st);
-    return launch_direct_cfg<CfgDirectKC, false, false>(g, st);
+    if (!g.a_kc) {
+      if (g.add_count != 0) return hipErrorInvalidValue;
+      return p.mid ? launch_direct_cfg<CfgMidRC, true>(g, p.splits, st)
+                   : launch_direct_cfg<CfgBigRC, true>(g, p.splits, st);
+    }
+    return p.mid ? launch_direct_cfg<CfgMidKC, false>(g, p.splits, st)
+                 : launch_direct_cfg<CfgBigKC, false>(g, p.splits, st);
   }
   if (g.Cb) return hipErrorInvalidValue;  // a bf16 result needs the direct path
   if (hipError_t e = gemm_staged_launch(g, st)) return e;
