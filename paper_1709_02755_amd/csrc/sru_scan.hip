@@ -365,6 +365,75 @@ constexpr int kNrUnits = 64;
 constexpr int kNrSteps = 16;  // steps per hand-off
 constexpr int kNrSlots = 4;   // groups in the ring
 
+// The producer wave of the narrow ring: group gi of kNrSteps steps into slot
+// gi % SLOTS, kNrSlots - 1 groups ahead of the group `it` it hands over at
+// each of `meets` barriers.
+template <int KB, bool MASK, int SLOTS>
+__device__ __forceinline__ void nring_produce(const ScanShape& s, const ScanFwdArgs& a,
+                                              unsigned u_bytes, unsigned x_bytes, unsigned m_bytes,
+                                              unsigned char* ring, unsigned (*mring)[64], int b,
+                                              int dir, int jb, bool rev, int lane, int meets) {
+  constexpr int NSEG = 4;  // U blocks 0-2 and x (k = 3), or U blocks 0-3 (k = 4)
+  constexpr int STEPB = kNrUnits * 4;        // one segment of one step
+  constexpr int SEGB = kNrSteps * STEPB;     // one segment of a group
+  constexpr int SLOTB = NSEG * SEGB;
+  constexpr int IPG = NSEG * (kNrSteps / 4) + (MASK ? 1 : 0);  // loads per group
+  static_assert((kNrSlots - 1) * IPG < 64, "vmcnt counts at most 63 loads");
+  const int L = s.L;
+  const int G = (L + kNrSteps - 1) / kNrSteps;
+  const __amdgpu_buffer_rsrc_t ru = ring_rsrc(a.U, u_bytes);
+  const __amdgpu_buffer_rsrc_t rx = ring_rsrc(KB == 3 ? a.X : a.U, KB == 3 ? x_bytes : u_bytes);
+  const __amdgpu_buffer_rsrc_t rm =
+      ring_rsrc(MASK ? static_cast<const void*>(a.mask) : static_cast<const void*>(a.U),
+                MASK ? m_bytes : u_bytes);
+  const unsigned u_step = (unsigned)s.B * s.ndir * KB * s.d * 4u;
+  const unsigned x_step = (unsigned)s.B * s.d_in * 4u;
+  const int sub = lane >> 4;                    // step of the four an instruction loads
+  const unsigned uc = (unsigned)(lane & 15) * 16u;  // the lane's four units
+  const unsigned u_base =
+      (unsigned)((((long long)b * s.ndir + dir) * KB * s.d + jb * kNrUnits) * 4) + uc;
+  const unsigned x_base = (unsigned)(((long long)b * s.d_in + jb * kNrUnits) * 4) + uc;
+  const unsigned seg = (unsigned)s.d * 4u;
+  auto issue = [&](int gi) {
+    unsigned char* slot = ring + (gi % SLOTS) * SLOTB;
+#pragma unroll
+    for (int k4 = 0; k4 < kNrSteps / 4; ++k4) {
+      const int step = gi * kNrSteps + 4 * k4 + sub;
+      const bool in = step < L;
+      const unsigned t = in ? (unsigned)(rev ? L - 1 - step : step) : 0u;
+      const unsigned oob = in ? 0u : kRingOOB;
+      const unsigned uo = (t * u_step + u_base) | oob;
+#pragma unroll
+      for (int q = 0; q < KB; ++q)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            ru, (lds_t*)(slot + q * SEGB + k4 * 4 * STEPB), 16, uo + q * seg, 0, 0, 0);
+      if constexpr (KB == 3)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rx, (lds_t*)(slot + 3 * SEGB + k4 * 4 * STEPB), 16, (t * x_step + x_base) | oob, 0,
+            0, 0);
+    }
+    if constexpr (MASK) {
+      const int step = gi * kNrSteps + lane;
+      const bool in = lane < kNrSteps && step < L;
+      const unsigned t = in ? (unsigned)(rev ? L - 1 - step : step) : 0u;
+      const unsigned mo = in ? t * (unsigned)s.B + (unsigned)b : kRingOOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rm, (lds_t*)(&mring[gi % SLOTS][0]), 1, mo, 0,
+                                               0, 0);
+    }
+  };
+  for (int gi = 0; gi < kNrSlots - 1 && gi < G; ++gi) issue(gi);
+  for (int it = 0; it < meets; ++it) {
+    // group it has landed once at most the groups issued after it remain
+    const int later = min(kNrSlots - 2, G - 1 - it);
+    if (later >= 2) __builtin_amdgcn_s_waitcnt(ring_vm_wait(2 * IPG));
+    else if (later == 1) __builtin_amdgcn_s_waitcnt(ring_vm_wait(IPG));
+    else __builtin_amdgcn_s_waitcnt(ring_vm_wait(0));
+    ring_barrier();
+    // a slot that every reader finished before the barrier
+    if (it + kNrSlots - 1 < G) issue(it + kNrSlots - 1);
+  }
+}
+
 template <int KB, bool MASK, bool STORE_C, bool STORE_HB, bool RN>
 __global__ __launch_bounds__(128) void scan_fwd_nring_kernel(ScanShape s, ScanFwdArgs a,
                                                              unsigned u_bytes, unsigned x_bytes,
@@ -373,8 +442,6 @@ __global__ __launch_bounds__(128) void scan_fwd_nring_kernel(ScanShape s, ScanFw
   constexpr int STEPB = kNrUnits * 4;        // one segment of one step
   constexpr int SEGB = kNrSteps * STEPB;     // one segment of a group
   constexpr int SLOTB = NSEG * SEGB;
-  constexpr int IPG = NSEG * (kNrSteps / 4) + (MASK ? 1 : 0);  // loads per group
-  static_assert((kNrSlots - 1) * IPG < 64, "vmcnt counts at most 63 loads");
   __shared__ __attribute__((aligned(1024))) unsigned char ring[kNrSlots * SLOTB];
   __shared__ __attribute__((aligned(256))) unsigned mring[kNrSlots][64];
 
@@ -390,58 +457,8 @@ __global__ __launch_bounds__(128) void scan_fwd_nring_kernel(ScanShape s, ScanFw
   const int lane = threadIdx.x & 63;
 
   if (wave == 1) {
-    // ---- producer
-    const __amdgpu_buffer_rsrc_t ru = ring_rsrc(a.U, u_bytes);
-    const __amdgpu_buffer_rsrc_t rx = ring_rsrc(KB == 3 ? a.X : a.U, KB == 3 ? x_bytes : u_bytes);
-    const __amdgpu_buffer_rsrc_t rm =
-        ring_rsrc(MASK ? static_cast<const void*>(a.mask) : static_cast<const void*>(a.U),
-                  MASK ? m_bytes : u_bytes);
-    const unsigned u_step = (unsigned)s.B * s.ndir * KB * s.d * 4u;
-    const unsigned x_step = (unsigned)s.B * s.d_in * 4u;
-    const int sub = lane >> 4;                    // step of the four an instruction loads
-    const unsigned uc = (unsigned)(lane & 15) * 16u;  // the lane's four units
-    const unsigned u_base =
-        (unsigned)((((long long)b * s.ndir + dir) * KB * s.d + jb * kNrUnits) * 4) + uc;
-    const unsigned x_base = (unsigned)(((long long)b * s.d_in + jb * kNrUnits) * 4) + uc;
-    const unsigned seg = (unsigned)s.d * 4u;
-    auto issue = [&](int gi) {
-      unsigned char* slot = ring + (gi % kNrSlots) * SLOTB;
-#pragma unroll
-      for (int k4 = 0; k4 < kNrSteps / 4; ++k4) {
-        const int step = gi * kNrSteps + 4 * k4 + sub;
-        const bool in = step < L;
-        const unsigned t = in ? (unsigned)(rev ? L - 1 - step : step) : 0u;
-        const unsigned oob = in ? 0u : kRingOOB;
-        const unsigned uo = (t * u_step + u_base) | oob;
-#pragma unroll
-        for (int q = 0; q < KB; ++q)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(
-              ru, (lds_t*)(slot + q * SEGB + k4 * 4 * STEPB), 16, uo + q * seg, 0, 0, 0);
-        if constexpr (KB == 3)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(
-              rx, (lds_t*)(slot + 3 * SEGB + k4 * 4 * STEPB), 16, (t * x_step + x_base) | oob, 0,
-              0, 0);
-      }
-      if constexpr (MASK) {
-        const int step = gi * kNrSteps + lane;
-        const bool in = lane < kNrSteps && step < L;
-        const unsigned t = in ? (unsigned)(rev ? L - 1 - step : step) : 0u;
-        const unsigned mo = in ? t * (unsigned)s.B + (unsigned)b : kRingOOB;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rm, (lds_t*)(&mring[gi % kNrSlots][0]), 1, mo, 0,
-                                                 0, 0);
-      }
-    };
-    for (int gi = 0; gi < kNrSlots - 1 && gi < G; ++gi) issue(gi);
-    for (int g = 0; g < G; ++g) {
-      // group g has landed once at most the groups issued after it remain
-      const int later = min(kNrSlots - 2, G - 1 - g);
-      if (later >= 2) __builtin_amdgcn_s_waitcnt(ring_vm_wait(2 * IPG));
-      else if (later == 1) __builtin_amdgcn_s_waitcnt(ring_vm_wait(IPG));
-      else __builtin_amdgcn_s_waitcnt(ring_vm_wait(0));
-      ring_barrier();
-      // the slot of group g - 1, which the consumer finished before the barrier
-      if (g + kNrSlots - 1 < G) issue(g + kNrSlots - 1);
-    }
+    nring_produce<KB, MASK, kNrSlots>(s, a, u_bytes, x_bytes, m_bytes, ring, mring, b, dir, jb, rev,
+                                      lane, G);
     return;
   }
 
@@ -503,6 +520,126 @@ __global__ __launch_bounds__(128) void scan_fwd_nring_kernel(ScanShape s, ScanFw
     }
   }
   if (a.c_last) a.c_last[gid] = c;
+}
+
+// ------------------------------------ forward scan, narrow ring in two waves
+// The narrow ring with the recurrence and its outputs in two waves.  At one
+// wave per SIMD a step is bound by its instructions (about 37, four cycles
+// each: 70 ns), not by the chain from one c to the next (six dependent
+// operations).  Here one wave carries c alone (Eq. 1-2: two LDS reads, seven
+// operations) and leaves every state in LDS; another, one group of steps
+// behind, computes the reset gate, h and the stores (Eq. 3-4); a third is
+// the producer.  The ring has one more slot, for the group the output wave
+// still reads.  Same arithmetic, same bits.  L 256, B 8, d 1024: 18.1 ->
+// 14.8 us; L 400, B 32, d 128, both directions: 29.4 -> 26.8 us.
+// What is left is the chain itself, 56-60 ns a step.
+constexpr int kDuoSlots = kNrSlots + 1;
+
+template <int KB, bool MASK, bool STORE_C, bool STORE_HB, bool RN>
+__global__ __launch_bounds__(192) void scan_fwd_duo_kernel(ScanShape s, ScanFwdArgs a,
+                                                           unsigned u_bytes, unsigned x_bytes,
+                                                           unsigned m_bytes) {
+  constexpr int STEPB = kNrUnits * 4;
+  constexpr int SEGB = kNrSteps * STEPB;
+  constexpr int SLOTB = 4 * SEGB;
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[kDuoSlots * SLOTB];
+  __shared__ __attribute__((aligned(256))) unsigned mring[kDuoSlots][64];
+  __shared__ float cring[2][kNrSteps][kNrUnits];
+
+  const int nblk = s.d / kNrUnits;
+  const int jb = blockIdx.x % nblk;
+  const int bd = blockIdx.x / nblk;
+  const int dir = bd % s.ndir;
+  const int b = bd / s.ndir;
+  const bool rev = s.direction == 1 || (s.direction == 2 && dir == 1);
+  const int L = s.L;
+  const int G = (L + kNrSteps - 1) / kNrSteps;
+  const int wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  // iteration it of every wave starts at a barrier: the recurrence runs group
+  // it, the outputs group it - 1
+  if (wave == 2) {
+    nring_produce<KB, MASK, kDuoSlots>(s, a, u_bytes, x_bytes, m_bytes, ring, mring, b, dir, jb,
+                                       rev, lane, G + 1);
+    return;
+  }
+  // padding of group g's steps, one scalar bit each
+  auto pad_bits = [&](int g) -> unsigned long long {
+    if constexpr (!MASK) return 0;
+    return __ballot(lane < kNrSteps && (mring[g % kDuoSlots][lane] & 0xFFu) != 0);
+  };
+  const int fidx = dir * s.d + jb * kNrUnits + lane;
+  const long long nfeat = (long long)s.ndir * s.d;
+  const long long gid = (long long)b * nfeat + fidx;
+  float c = a.c0 ? a.c0[gid] : 0.0f;
+
+  if (wave == 0) {
+    const float vfs = a.v_f[fidx] * kNegLog2e, bfs = a.b_f[fidx] * kNegLog2e;
+    for (int it = 0; it < G; ++it) {
+      ring_barrier();
+      const unsigned char* slot = ring + (it % kDuoSlots) * SLOTB + lane * 4;
+      const unsigned long long pads = pad_bits(it);
+      float* cw = &cring[it & 1][0][lane];
+      auto step = [&](int st) {
+        const float u0 = *reinterpret_cast<const float*>(slot + st * STEPB);
+        const float u1 = *reinterpret_cast<const float*>(slot + SEGB + st * STEPB);
+        const float f = sigmoid_scaled(fmaf(vfs, c, fmaf(u1, kNegLog2e, bfs)));  // Eq. 1
+        const float cn = fmaf(f, c, fmaf(-f, u0, u0));                           // Eq. 2
+        if constexpr (MASK) c = (pads >> st) & 1 ? c : cn;
+        else c = cn;
+        cw[st * kNrUnits] = c;
+      };
+      if ((it + 1) * kNrSteps <= L) {
+#pragma unroll
+        for (int st = 0; st < kNrSteps; ++st) step(st);
+      } else {
+        for (int st = 0; it * kNrSteps + st < L; ++st) step(st);
+      }
+    }
+    ring_barrier();
+    if (a.c_last) a.c_last[gid] = c;
+    return;
+  }
+
+  const float vrs = a.v_r[fidx] * kNegLog2e, brs = a.b_r[fidx] * kNegLog2e;
+  const float alpha = s.alpha;
+  // bases of the workgroup's outputs, the same for the whole wave
+  const long long h_step = (long long)s.B * nfeat;
+  const long long sh = rev ? -h_step : h_step;
+  const long long o0 = (long long)b * nfeat + dir * s.d + jb * kNrUnits + (rev ? L - 1 : 0) * h_step;
+  float* hp = a.H + o0;
+  float* cp = STORE_C ? a.C + o0 : nullptr;
+  uint16_t* hbp = STORE_HB ? a.Hb + o0 : nullptr;
+  ring_barrier();
+  for (int it = 1; it <= G; ++it) {
+    ring_barrier();
+    const int g = it - 1;
+    const unsigned char* slot = ring + (g % kDuoSlots) * SLOTB + lane * 4;
+    const unsigned long long pads = pad_bits(g);
+    const float* cr = &cring[g & 1][0][lane];
+    auto step = [&](int st) {
+      const float u2 = *reinterpret_cast<const float*>(slot + 2 * SEGB + st * STEPB);
+      const float xh = *reinterpret_cast<const float*>(slot + 3 * SEGB + st * STEPB);
+      const float cn = cr[st * kNrUnits];  // the state after the step
+      const float r = sigmoid_scaled(fmaf(vrs, RN ? cn : c, fmaf(u2, kNegLog2e, brs)));  // Eq. 3
+      float h = fmaf(r, cn, (1.0f - r) * (alpha * xh));  // Eq. 4 (Sec. 3.2)
+      if constexpr (MASK) h = (pads >> st) & 1 ? 0.0f : h;
+      c = cn;
+      __builtin_nontemporal_store(h, hp + lane);
+      if constexpr (STORE_C) __builtin_nontemporal_store(cn, cp + lane);
+      if constexpr (STORE_HB)
+        __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, (__bf16)h), hbp + lane);
+      hp += sh;
+      if constexpr (STORE_C) cp += sh;
+      if constexpr (STORE_HB) hbp += sh;
+    };
+    if ((g + 1) * kNrSteps <= L) {
+#pragma unroll
+      for (int st = 0; st < kNrSteps; ++st) step(st);
+    } else {
+      for (int st = 0; g * kNrSteps + st < L; ++st) step(st);
+    }
+  }
 }
 
 template <int KB, bool MASK, bool DUB, bool RN, int PF>
@@ -700,13 +837,14 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Lane of a chunked workgroup: as decode_lane, with the lane index taken
-// from threadIdx.x mod 64.  Lanes past the end (live = false) take the last
+// from threadIdx.x mod LW.  Lanes past the end (live = false) take the last
 // lane's coordinates, so every address they form is in range; they store
-// nothing.
+// nothing.  LW: lanes per workgroup (a wave of 64 threads is 64 / LW chunks).
+template <int LW>
 __device__ __forceinline__ bool decode_lane_lin(const ScanShape& s, Lane& ln, int group) {
   const int nfeat = s.ndir * s.d;
   const int total = s.B * nfeat;
-  const int gid = group * 64 + (threadIdx.x & 63);
+  const int gid = group * LW + (threadIdx.x & (LW - 1));
   const bool live = gid < total;
   ln.gid = live ? gid : total - 1;
   ln.b = ln.gid / nfeat;
@@ -735,7 +873,7 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_lin_maps_kernel(ScanSh
   __shared__ float2 red[kLinMaxWaves][64];
   Lane ln;
   const int group = blockIdx.x % pl.groups, seg = blockIdx.x / pl.groups;
-  const bool live = decode_lane_lin(s, ln, group);
+  const bool live = decode_lane_lin<64>(s, ln, group);
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
@@ -806,18 +944,18 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_lin_maps_kernel(ScanSh
   }
 }
 
-template <int KB, bool MASK, bool STORE_C, bool STORE_HB, int CH>
-__global__ __launch_bounds__(64 * kLinMaxWaves) void scan_fwd_lin_kernel(ScanShape s,
+template <int KB, bool MASK, bool STORE_C, bool STORE_HB, int CH, int LW>
+__global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_fwd_lin_kernel(ScanShape s,
                                                                          ScanFwdArgs a,
                                                                          LinPlan pl) {
-  __shared__ float2 agg[2][kLinMaxWaves][64];  // (A, S) per block parity, wave, lane
-  __shared__ float carry_lds[2][64];           // block's final state, per parity
+  __shared__ float2 agg[2][kLinMaxWaves][LW];  // (A, S) per block parity, wave, lane
+  __shared__ float carry_lds[2][LW];           // block's final state, per parity
   Lane ln;
   const int group = blockIdx.x % pl.groups, seg = blockIdx.x / pl.groups;
-  const bool live = decode_lane_lin(s, ln, group);
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int NW = blockDim.x >> 6;
+  const bool live = decode_lane_lin<LW>(s, ln, group);
+  const int lane = threadIdx.x & (LW - 1);
+  const int w = threadIdx.x / LW;  // the chunk of a block this thread works on
+  const int NW = blockDim.x / LW;
   const int L = s.L;
   const int d = s.d;
   const long long nfeat = (long long)s.ndir * s.d;
@@ -917,18 +1055,18 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_fwd_lin_kernel(ScanSha
 //   g <- gc f          (the map g -> f g + f dh r)
 // b_f / b_r sums go to partial[b][2|3][feature] after a fixed-order sum
 // over the workgroup's waves.
-template <int KB, bool MASK, bool DUB, int CH>
-__global__ __launch_bounds__(64 * kLinMaxWaves) void scan_bwd_lin_kernel(ScanShape s,
+template <int KB, bool MASK, bool DUB, int CH, int LW>
+__global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_lin_kernel(ScanShape s,
                                                                          ScanBwdArgs a,
                                                                          LinPlan pl) {
-  __shared__ float2 agg[2][kLinMaxWaves][64];
-  __shared__ float carry_lds[2][64];
+  __shared__ float2 agg[2][kLinMaxWaves][LW];
+  __shared__ float carry_lds[2][LW];
   Lane ln;
   const int group = blockIdx.x % pl.groups, seg = blockIdx.x / pl.groups;
-  const bool live = decode_lane_lin(s, ln, group);
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int NW = blockDim.x >> 6;
+  const bool live = decode_lane_lin<LW>(s, ln, group);
+  const int lane = threadIdx.x & (LW - 1);
+  const int w = threadIdx.x / LW;  // the chunk of a block this thread works on
+  const int NW = blockDim.x / LW;
   const int L = s.L;
   const int d = s.d;
   const long long nfeat = (long long)s.ndir * s.d;
@@ -1085,17 +1223,17 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_bwd_lin_kernel(ScanSha
 // lanes covers the whole sequence (no time segments), so this serves shapes
 // whose lane groups alone fill at least half the CUs and leave most SIMDs
 // without a wave; there the sequential scan waits on its serial chain.
-template <int KB, bool MASK, bool DUB, bool RN, int CH>
-__global__ __launch_bounds__(64 * kLinMaxWaves) void scan_bwd_tp_kernel(ScanShape s,
+template <int KB, bool MASK, bool DUB, bool RN, int CH, int LW>
+__global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_tp_kernel(ScanShape s,
                                                                         ScanBwdArgs a,
                                                                         LinPlan pl) {
-  __shared__ float2 agg[2][kLinMaxWaves][64];
-  __shared__ float carry_lds[2][64];
+  __shared__ float2 agg[2][kLinMaxWaves][LW];
+  __shared__ float carry_lds[2][LW];
   Lane ln;
-  const bool live = decode_lane_lin(s, ln, blockIdx.x);
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int NW = blockDim.x >> 6;
+  const bool live = decode_lane_lin<LW>(s, ln, blockIdx.x);
+  const int lane = threadIdx.x & (LW - 1);
+  const int w = threadIdx.x / LW;  // the chunk of a block this thread works on
+  const int NW = blockDim.x / LW;
   const int L = s.L;
   const int d = s.d;
   const long long nfeat = (long long)s.ndir * s.d;
@@ -1298,6 +1436,18 @@ LinPlan lin_plan(const ScanShape& s, int ch) {
   return pl;
 }
 
+// Workgroups of 32 lanes, each wave two chunks, where 64-lane groups would
+// leave half of the CUs without a workgroup (and time is not cut into
+// segments): the same chunks and bits on twice the CUs with half the waves per
+// SIMD.  Gated backward, 8,192 lanes: 23.5 -> 20.7 us (L 256), 37.9 -> 32.3
+// us (L 400); 12,288 lanes: 27.7 -> 34.4 us, since 384 workgroups are one and
+// a half per CU.
+bool half_lanes(const LinPlan& pl) { return pl.nseg == 1 && pl.groups <= 128 && pl.nw >= 2; }
+LinPlan half_plan(LinPlan pl) {
+  pl.groups *= 2;
+  return pl;
+}
+
 template <int KB, bool MASK, bool STORE_C, bool STORE_HB>
 hipError_t fwd_lin_dispatch(const ScanShape& s, const ScanFwdArgs& a, hipStream_t st) {
   const LinPlan pl = lin_plan(s, kFwdLinCH);
@@ -1310,8 +1460,12 @@ hipError_t fwd_lin_dispatch(const ScanShape& s, const ScanFwdArgs& a, hipStream_
     if (hipError_t e = hipGetLastError()) return e;
   }
   timing_before("scan_fwd", st);
-  hipLaunchKernelGGL((scan_fwd_lin_kernel<KB, MASK, STORE_C, STORE_HB, kFwdLinCH>),
-                     dim3(pl.groups * pl.nseg), dim3(64 * pl.nw), 0, st, s, a, pl);
+  if (half_lanes(pl))
+    hipLaunchKernelGGL((scan_fwd_lin_kernel<KB, MASK, STORE_C, STORE_HB, kFwdLinCH, 32>),
+                       dim3(2 * pl.groups), dim3(32 * pl.nw), 0, st, s, a, half_plan(pl));
+  else
+    hipLaunchKernelGGL((scan_fwd_lin_kernel<KB, MASK, STORE_C, STORE_HB, kFwdLinCH, 64>),
+                       dim3(pl.groups * pl.nseg), dim3(64 * pl.nw), 0, st, s, a, pl);
   timing_after(st);
   return hipGetLastError();
 }
@@ -1345,6 +1499,12 @@ bool nring_ok(const ScanShape& s, long long u_bytes, long long x_bytes) {
          (long long)s.L * s.B < (long long)kRingOOB;
 }
 
+// The two-wave form of the narrow ring holds 88 KiB of LDS, one workgroup per
+// CU: it runs where that is all of them.
+bool duo_ok(const ScanShape& s) {
+  return (long long)s.B * s.ndir * (s.d / kNrUnits) <= 256;
+}
+
 template <int KB, bool MASK, bool STORE_C, bool STORE_HB>
 hipError_t fwd_dispatch(const ScanShape& s, const ScanFwdArgs& a, hipStream_t st) {
   const int lanes = s.B * s.ndir * s.d;
@@ -1359,7 +1519,13 @@ hipError_t fwd_dispatch(const ScanShape& s, const ScanFwdArgs& a, hipStream_t st
     const int ngrid = s.B * s.ndir * (s.d / kNrUnits);
     const unsigned m_bytes = (unsigned)((long long)s.L * s.B);
     timing_before("scan_fwd", st);
-    if (s.reset_new)
+    if (duo_ok(s) && s.reset_new)
+      hipLaunchKernelGGL((scan_fwd_duo_kernel<KB, MASK, STORE_C, STORE_HB, true>), dim3(ngrid),
+                         dim3(192), 0, st, s, a, (unsigned)u_bytes, (unsigned)x_bytes, m_bytes);
+    else if (duo_ok(s))
+      hipLaunchKernelGGL((scan_fwd_duo_kernel<KB, MASK, STORE_C, STORE_HB, false>), dim3(ngrid),
+                         dim3(192), 0, st, s, a, (unsigned)u_bytes, (unsigned)x_bytes, m_bytes);
+    else if (s.reset_new)
       hipLaunchKernelGGL((scan_fwd_nring_kernel<KB, MASK, STORE_C, STORE_HB, true>), dim3(ngrid),
                          dim3(128), 0, st, s, a, (unsigned)u_bytes, (unsigned)x_bytes, m_bytes);
     else
@@ -1441,6 +1607,30 @@ void bwd_launch(const ScanShape& s, const ScanBwdArgs& a, int grid, hipStream_t 
                        dim3(kScanThreads), 0, st, s, a);
 }
 
+template <int KB, bool MASK, int LW>
+void bwd_lin_launch(const ScanShape& s, const ScanBwdArgs& a, const LinPlan& pl, int grid,
+                    hipStream_t st) {
+  const dim3 g(grid), b(LW * pl.nw);
+  if (a.du_bf16)
+    hipLaunchKernelGGL((scan_bwd_lin_kernel<KB, MASK, true, kBwdLinCH, LW>), g, b, 0, st, s, a, pl);
+  else
+    hipLaunchKernelGGL((scan_bwd_lin_kernel<KB, MASK, false, kBwdLinCH, LW>), g, b, 0, st, s, a, pl);
+}
+
+template <int KB, bool MASK, int LW>
+void bwd_tp_launch(const ScanShape& s, const ScanBwdArgs& a, const LinPlan& pl, int grid,
+                   hipStream_t st) {
+  const dim3 g(grid), b(LW * pl.nw);
+  if (a.du_bf16 && s.reset_new)
+    hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, true, true, kBwdTpCH, LW>), g, b, 0, st, s, a, pl);
+  else if (a.du_bf16)
+    hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, true, false, kBwdTpCH, LW>), g, b, 0, st, s, a, pl);
+  else if (s.reset_new)
+    hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, false, true, kBwdTpCH, LW>), g, b, 0, st, s, a, pl);
+  else
+    hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, false, false, kBwdTpCH, LW>), g, b, 0, st, s, a, pl);
+}
+
 template <int KB, bool MASK>
 hipError_t bwd_dispatch(const ScanShape& s, const ScanBwdArgs& a, hipStream_t st) {
   const int lanes = s.B * s.ndir * s.d;
@@ -1456,27 +1646,16 @@ hipError_t bwd_dispatch(const ScanShape& s, const ScanBwdArgs& a, hipStream_t st
       if (hipError_t e = hipGetLastError()) return e;
     }
     timing_before("scan_bwd", st);
-    if (a.du_bf16)
-      hipLaunchKernelGGL((scan_bwd_lin_kernel<KB, MASK, true, kBwdLinCH>),
-                         dim3(pl.groups * pl.nseg), dim3(64 * pl.nw), 0, st, s, a, pl);
-    else
-      hipLaunchKernelGGL((scan_bwd_lin_kernel<KB, MASK, false, kBwdLinCH>),
-                         dim3(pl.groups * pl.nseg), dim3(64 * pl.nw), 0, st, s, a, pl);
+    if (half_lanes(pl)) bwd_lin_launch<KB, MASK, 32>(s, a, half_plan(pl), 2 * pl.groups, st);
+    else bwd_lin_launch<KB, MASK, 64>(s, a, pl, pl.groups * pl.nseg, st);
     timing_after(st);
     return hipGetLastError();
   }
   if (bwd_tp_ok(s)) {
     const LinPlan pl = lin_plan(s, kBwdTpCH);
-    const dim3 g(pl.groups), b(64 * pl.nw);
     timing_before("scan_bwd", st);
-    if (a.du_bf16 && s.reset_new)
-      hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, true, true, kBwdTpCH>), g, b, 0, st, s, a, pl);
-    else if (a.du_bf16)
-      hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, true, false, kBwdTpCH>), g, b, 0, st, s, a, pl);
-    else if (s.reset_new)
-      hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, false, true, kBwdTpCH>), g, b, 0, st, s, a, pl);
-    else
-      hipLaunchKernelGGL((scan_bwd_tp_kernel<KB, MASK, false, false, kBwdTpCH>), g, b, 0, st, s, a, pl);
+    if (half_lanes(pl)) bwd_tp_launch<KB, MASK, 32>(s, a, half_plan(pl), 2 * pl.groups, st);
+    else bwd_tp_launch<KB, MASK, 64>(s, a, pl, pl.groups, st);
     timing_after(st);
     return hipGetLastError();
   }
