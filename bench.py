@@ -34,7 +34,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
-MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}
+# fp32 products take six bf16 matrix products each
+MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 2500.0 / 6}
 
 
 def log(msg):
@@ -168,6 +169,7 @@ def _layer_work(w, li, splits, bf16):
         "proj_scan_fwd": dict(flops=2.0 * M * N * K),
         "gemm_dx": dict(flops=2.0 * M * K * N),    # dX = dU W
         "gemm_dw": dict(flops=2.0 * N * K * M),    # dW = dU^T X
+        "gemm_dx_dw": dict(flops=4.0 * N * K * M),  # both in one launch
         # read U's three blocks and x_hat (x, or U block 3), write h and c
         # (24 B per (t, b, j); 20 B without c); with bf16 products below the
         # top layer also the bf16 copy of h (the next layer's operand)

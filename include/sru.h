@@ -337,7 +337,8 @@ SRU_API int sru_scan_backward(const float* U, const float* X, const float* C, co
  * out, further kernels are not bracketed.  sru_timing_end disarms the hook
  * and returns the number of kernels bracketed; sru_timing_label(i) names
  * kernel i until the next sru_timing_begin ("" out of range):
- *   products: "gemm_u", "gemm_dx", "gemm_dw" (layer calls), "gemm_t",
+ *   products: "gemm_u", "gemm_dx", "gemm_dw", "gemm_dx_dw" (the two in one
+ *     launch, at sizes that leave CUs idle; layer calls), "gemm_t",
  *     "gemm_dt", "gemm_dp", "gemm_dq" (low-rank calls), "gemm_nt",
  *     "gemm_nn", "gemm_tn" (sru_gemm), "splitk_reduce";
  *   bf16 operand copies: "bf16_w", "bf16_x", "bf16_wt", "bf16_q", "bf16_p",

@@ -219,12 +219,13 @@ sru::GemmDesc dw_desc(const Dims& s, bool bf16, const void* dU, const void* X, f
 //    Wcat^T and X in bf16 (bf16 mode) | split partials]
 // The split partials of dW and dX share one region, each product's sum
 // running before the other product starts; when both are split and dX runs
-// first, dX's sum runs in dW's split-sum launch (one launch less), and dX's
-// partials then follow dW's.
+// first or with dW, dX's sum runs in dW's split-sum launch (one launch less),
+// and dX's partials then follow dW's.
 struct BwdLayout {
   size_t dU, dxh, partial, wt, xb, splitk, splitk_dx, total;
   int splits, splits_dx;
   bool joint_sum;
+  sru::GemmPair pair;  // dX and dW in one launch (splits_x > 0)
 };
 
 // dX = dU Wcat (+ highway): NN on Wcat in fp32 mode; in bf16 mode NT on the
@@ -266,8 +267,12 @@ BwdLayout bwd_layout(const Dims& s, int gemm_dtype) {
   if (bf16) off += align_up(2 * (size_t)s.N * (size_t)s.d_in);
   w.xb = off;
   if (bf16) off += align_up(2 * (size_t)s.M * (size_t)s.d_in);
-  w.splits = sru::gemm_splits(dw_desc(s, bf16, nullptr, nullptr, nullptr));
-  w.splits_dx = sru::gemm_splits(dx_desc(s, bf16, nullptr, nullptr, nullptr, nullptr, nullptr));
+  const sru::GemmDesc gw = dw_desc(s, bf16, nullptr, nullptr, nullptr);
+  const sru::GemmDesc gx = dx_desc(s, bf16, nullptr, nullptr, nullptr, nullptr, nullptr);
+  if (!dx_last(s)) w.pair = sru::gemm_pair_plan(gx, gw);
+  const bool paired = w.pair.splits_x > 0;
+  w.splits = paired ? w.pair.splits_w : sru::gemm_splits(gw);
+  w.splits_dx = paired ? w.pair.splits_x : sru::gemm_splits(gx);
   w.joint_sum = w.splits > 1 && w.splits_dx > 1 && !dx_last(s);
   const size_t pw = sru::gemm_partial_bytes((int)s.N, s.d_in, w.splits);
   const size_t px = sru::gemm_partial_bytes((int)s.M, s.d_in, w.splits_dx);
@@ -628,6 +633,11 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
   const void* Xop = !bf16 ? static_cast<const void*>(X) : X_bf16 ? X_bf16 : xb;
   sru::GemmDesc gw = dw_desc(s, bf16, dU, Xop, dW);
   gw.partials = splitk;
+  const bool paired = lay.pair.splits_x > 0;
+  if (paired) {
+    gw.plan_tile = lay.pair.tile;
+    gw.plan_splits = lay.pair.splits_w;
+  }
   // the split partials were sized for lay.splits; refuse (before enqueueing
   // anything) rather than overrun if the launch plan ever differed
   if (sru::gemm_splits(gw) > lay.splits) return SRU_E_WORKSPACE;
@@ -651,15 +661,20 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
   //    rounded from W), both operands K-contiguous, so it runs at the speed
   //    of the projection.  Split partials: see BwdLayout (with both
   //    products split and dX first, one launch sums both).
+  auto round_x = [&]() -> int {
+    if (!bf16 || X_bf16) return SRU_OK;
+    return hip_status(sru::to_bf16_launch(X, (int)s.M, d_in, xb, false, stream, "bf16_x"));
+  };
   auto run_dw = [&]() -> int {
-    if (bf16 && !X_bf16) {
-      if (int e = hip_status(sru::to_bf16_launch(X, (int)s.M, d_in, xb, false, stream, "bf16_x")))
-        return e;
-    }
+    if (int e = round_x()) return e;
     return hip_status(sru::gemm_launch(gw, stream));
   };
   sru::GemmDesc gx = dx_desc(s, bf16, dU, W, wt, dX, dxh);
   gx.partials = reinterpret_cast<float*>(ws + lay.splitk_dx);
+  if (paired) {
+    gx.plan_tile = lay.pair.tile;
+    gx.plan_splits = lay.pair.splits_x;
+  }
   // split as planned, else (a plan that differs at run time) not at all
   if (sru::gemm_splits(gx) > lay.splits_dx) gx.kc_split = false;
   if (lay.joint_sum && sru::gemm_splits(gx) > 1 && sru::gemm_splits(gw) > 1) {
@@ -667,15 +682,21 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
     gx.defer_sum = true;
     gw.extra = sru::gemm_split_sum(gx);
   }
+  auto transpose_w = [&]() -> int {
+    if (!bf16) return SRU_OK;
+    return hip_status(W_bf16
+        ? sru::to_bf16_t_launch(W_bf16, true, (int)s.N, d_in, wt, stream, "bf16_wt")
+        : sru::to_bf16_t_launch(W, false, (int)s.N, d_in, wt, stream, "bf16_wt"));
+  };
   auto run_dx = [&]() -> int {
-    if (bf16) {
-      const hipError_t te = W_bf16
-          ? sru::to_bf16_t_launch(W_bf16, true, (int)s.N, d_in, wt, stream, "bf16_wt")
-          : sru::to_bf16_t_launch(W, false, (int)s.N, d_in, wt, stream, "bf16_wt");
-      if (int e = hip_status(te)) return e;
-    }
+    if (int e = transpose_w()) return e;
     return hip_status(sru::gemm_launch(gx, stream));
   };
+  if (paired) {
+    if (int e = transpose_w()) return e;
+    if (int e = round_x()) return e;
+    return hip_status(sru::gemm_pair_launch(gx, gw, stream));
+  }
   if (dx_last(s)) {
     if (int e = run_dw()) return e;
     return run_dx();

@@ -555,11 +555,12 @@ __device__ __forceinline__ void direct_mainloop(unsigned char* smem, const OpA& 
   }
 }
 
+// Workgroup w of a product's nwg.  smem: C::LDS bytes.
 template <class C, int ADD, bool A_RC, bool B_RC, bool OB>
-__global__ __launch_bounds__(C::THREADS, C::OCC) void gemm_direct_kernel(KernelArgs g) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
-
-  const TileIdx ti = tile_of(g);
+__device__ __forceinline__ void direct_tile(const KernelArgs& g, int w, int nwg,
+                                            unsigned char* smem) {
+#ifdef __HIP_DEVICE_COMPILE__  // (the host pass fails to instantiate the main loop twice)
+  const TileIdx ti = tile_of(g, w, nwg);
   const int m0 = ti.tm * C::BM;
   const int n0 = ti.tn * C::BN;
   const int kbeg = ti.split * g.k_per_split;
@@ -599,7 +600,31 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void gemm_direct_kernel(KernelA
     }
   }
   write_tile_rows<C, ADD, OB>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+#endif
 }
+
+template <class C, int ADD, bool A_RC, bool B_RC, bool OB>
+__global__ __launch_bounds__(C::THREADS, C::OCC) void gemm_direct_kernel(KernelArgs g) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
+  direct_tile<C, ADD, A_RC, B_RC, OB>(g, blockIdx.x, gridDim.x, smem);
+}
+
+// dX (n1 workgroups) and dW (n2) on mid tiles in one launch, the one of longer
+// workgroups first.
+template <int ADD>
+__global__ __launch_bounds__(CfgMidKC::THREADS, 2) void gemm_direct_pair_kernel(KernelArgs g1, int n1,
+                                                                                KernelArgs g2, int n2,
+                                                                                bool dw_first) {
+  static_assert(CfgMidKC::THREADS == CfgMidRC::THREADS, "one block size");
+  __shared__ __attribute__((aligned(1024))) unsigned char
+      smem[CfgMidKC::LDS > CfgMidRC::LDS ? CfgMidKC::LDS : CfgMidRC::LDS];
+  const PairIdx p = pair_index(n1, n2, dw_first);
+  if (p.dx) direct_tile<CfgMidKC, ADD, false, false, false>(g1, p.w, n1, smem);
+  else direct_tile<CfgMidRC, 0, true, true, false>(g2, p.w, n2, smem);
+}
+template __global__ void gemm_direct_pair_kernel<0>(KernelArgs, int, KernelArgs, int, bool);
+template __global__ void gemm_direct_pair_kernel<1>(KernelArgs, int, KernelArgs, int, bool);
+template __global__ void gemm_direct_pair_kernel<2>(KernelArgs, int, KernelArgs, int, bool);
 
 // ---- fused projection + forward scan (inference: neither U nor C kept) ----
 // One workgroup per (direction, group of 64 hidden units, group of bb
@@ -1118,32 +1143,81 @@ struct DirectPlan {
   bool mid;
   int splits;
 };
-DirectPlan plan_direct(const GemmDesc& g) {
-  const bool rc = !g.a_kc;
+struct DirectRange {
+  int lo, hi;
+};
+DirectRange direct_range(const GemmDesc& g) {
   const int kt = (g.K + 63) / 64;
+  if (!split_allowed(g)) return {1, 1};
   // fewest splits whose row-contiguous panels fit (direct_ok: one stage does)
   long long kmax = kt;
-  if (rc) kmax = std::max(1LL, std::min({kmax, rc_max_k(g.M, g.lda) / 64, rc_max_k(g.N, g.ldb) / 64}));
-  const int s_min = split_allowed(g) ? (int)((kt + kmax - 1) / kmax) : 1;
-  const int s_max = split_allowed(g) ? std::max(s_min, kt / 6) : 1;
-  DirectPlan best{false, s_min};
+  if (!g.a_kc)
+    kmax = std::max(1LL, std::min({kmax, rc_max_k(g.M, g.lda) / 64, rc_max_k(g.N, g.ldb) / 64}));
+  const int lo = (int)((kt + kmax - 1) / kmax);
+  return {lo, std::max(lo, kt / 6)};
+}
+// every count up to 8, then steps of a quarter or less
+int next_direct_split(int s) { return s + std::max(1, s / 8); }
+long long direct_tiles(const GemmDesc& g, int b) {
+  return (long long)((g.M + b - 1) / b) * ((g.N + b - 1) / b);
+}
+double sum_traffic(const GemmDesc& g, int s) {
+  return s > 1 ? (s + 1) * 4.0 * g.M * g.N / 6.5e6 : 0.0;
+}
+// the real number of splits, each of whole K steps
+int real_direct_splits(const GemmDesc& g, int s) {
+  const int kt = (g.K + 63) / 64, per = (kt + s - 1) / s;
+  return (kt + per - 1) / per;
+}
+
+DirectPlan plan_direct(const GemmDesc& g, double* time = nullptr) {
+  if (g.plan_splits > 0) return {g.plan_tile != 0, g.plan_splits};
+  const int kt = (g.K + 63) / 64;
+  const DirectRange r = direct_range(g);
+  DirectPlan best{false, r.lo};
   double best_cost = -1.0;
   for (int m = 0; m < 2; ++m) {
-    const int b = m ? 128 : 256;
-    const long long tiles = (long long)((g.M + b - 1) / b) * ((g.N + b - 1) / b);
-    // every count up to 8, then steps of a quarter or less
-    for (int s = s_min; s <= s_max; s += std::max(1, s / 8)) {
-      const int steps = (kt + s - 1) / s;
-      double cost = direct_cost(m, rc, tiles * s, steps);
-      if (s > 1) cost += 2.0 + (s + 1) * 4.0 * g.M * g.N / 6.5e6;
+    const long long tiles = direct_tiles(g, m ? 128 : 256);
+    for (int s = r.lo; s <= r.hi; s = next_direct_split(s)) {
+      const double cost = direct_cost(m, !g.a_kc, tiles * s, (kt + s - 1) / s) +
+                          (s > 1 ? 2.0 + sum_traffic(g, s) : 0.0);
       if (best_cost < 0 || cost < best_cost) {
         best = {m != 0, s};
         best_cost = cost;
       }
     }
   }
-  const int per = (kt + best.splits - 1) / best.splits;
-  best.splits = (kt + per - 1) / per;  // the real number, each of whole K steps
+  best.splits = real_direct_splits(g, best.splits);
+  if (time) *time = best_cost;
+  return best;
+}
+
+// dX and dW together on mid tiles, where pair_time beats the two plans one
+// after the other.  L 256, B 8, d 1024: dX in 2 splits
+// and dW whole, 40 us and 6 for the sum, against 21 + 21 us and 12 (each in 2
+// splits).
+GemmPair direct_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
+  GemmPair best{0, 0, 0};
+  double tx, tw;
+  plan_direct(gx, &tx);
+  plan_direct(gw, &tw);
+  double best_cost = tx + tw;
+  const int kx = (gx.K + 63) / 64, kw = (gw.K + 63) / 64;
+  const DirectRange rx = direct_range(gx), rw = direct_range(gw);
+  const long long nx = direct_tiles(gx, 128), nw = direct_tiles(gw, 128);
+  for (int sx = rx.lo; sx <= rx.hi; sx = next_direct_split(sx)) {
+    const int stx = (kx + sx - 1) / sx;
+    for (int sw = rw.lo; sw <= rw.hi; sw = next_direct_split(sw)) {
+      const int stw = (kw + sw - 1) / sw;
+      const double cost = 3.0 + pair_time(nx * sx, stx, 0.62, nw * sw, stw, 0.85, 1.4, 0.51) +
+                          sum_traffic(gx, sx) + sum_traffic(gw, sw) +
+                          (sx > 1 || sw > 1 ? 2.0 : 0.0);
+      if (cost < best_cost) {
+        best = {1, real_direct_splits(gx, sx), real_direct_splits(gw, sw)};
+        best_cost = cost;
+      }
+    }
+  }
   return best;
 }
 
@@ -1163,8 +1237,8 @@ SRU_DIRECT_INST(CfgBigRC, 0, true, true, false)
 SRU_DIRECT_INST(CfgMidRC, 0, true, true, false)
 #undef SRU_DIRECT_INST
 
-template <class C, bool RC, bool OB = false>
-hipError_t launch_direct_cfg(const GemmDesc& g, int splits, hipStream_t st) {
+template <class C, bool OB = false>
+KernelArgs direct_args(const GemmDesc& g, int splits) {
   static_assert(C::BK == 64, "the plan counts 64-k steps");
   const int kt = (g.K + C::BK - 1) / C::BK;
   const int kps = ((kt + splits - 1) / splits) * C::BK;
@@ -1200,6 +1274,12 @@ hipError_t launch_direct_cfg(const GemmDesc& g, int splits, hipStream_t st) {
   a.vec_out = a.ldo % 4 == 0 && a.split_stride % 4 == 0 && (!a.out || al16(a.out)) &&
               (a.add_count == 0 || (a.add_ld % 4 == 0 && a.add_off % 4 == 0 && al16(a.add))) &&
               (!OB || (a.ldob % 4 == 0 && ((uintptr_t)a.outb & 7) == 0));
+  return a;
+}
+
+template <class C, bool RC, bool OB = false>
+hipError_t launch_direct_cfg(const GemmDesc& g, int splits, hipStream_t st) {
+  const KernelArgs a = direct_args<C, OB>(g, splits);
   const int nwg = a.tiles_m * a.tiles_n * splits;
   timing_before(gemm_label(g), st);
   if constexpr (OB) launch_direct<C, 0, RC, RC, true>(a, nwg, st);
@@ -1249,6 +1329,41 @@ hipError_t gemm_launch(const GemmDesc& g, hipStream_t st) {
   if (g.Cb) return hipErrorInvalidValue;  // a bf16 result needs the direct path
   if (hipError_t e = gemm_staged_launch(g, st)) return e;
   return finish_product(g, gemm_staged_splits(g), st);
+}
+
+GemmPair gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
+  const bool dx = direct_ok(gx), dw = direct_ok(gw);
+  if (dx != dw || gx.Cb || gw.Cb || gw.add_count != 0) return {0, 0, 0};
+  return dx ? direct_pair_plan(gx, gw) : gemm_staged_pair_plan(gx, gw);
+}
+
+hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t st) {
+  const bool dx = direct_ok(gx);
+  if (dx != direct_ok(gw) || (!dx && !gemm_staged_pair_launch(gx, gw, st))) {
+    // operands that need other loads than the plan assumed
+    if (hipError_t e = gemm_launch(gx, st)) return e;
+    return gemm_launch(gw, st);
+  }
+  if (dx) {
+    const KernelArgs a = direct_args<CfgMidKC>(gx, gx.plan_splits);
+    const KernelArgs b = direct_args<CfgMidRC>(gw, gw.plan_splits);
+    const int n1 = a.tiles_m * a.tiles_n * a.splits, n2 = b.tiles_m * b.tiles_n * b.splits;
+    const dim3 grid(n1 + n2), block(CfgMidKC::THREADS);
+    const bool dwf = b.k_per_split > a.k_per_split;
+    timing_before("gemm_dx_dw", st);
+    if (a.add_count == 2)
+      hipLaunchKernelGGL(gemm_direct_pair_kernel<2>, grid, block, 0, st, a, n1, b, n2, dwf);
+    else if (a.add_count == 1)
+      hipLaunchKernelGGL(gemm_direct_pair_kernel<1>, grid, block, 0, st, a, n1, b, n2, dwf);
+    else
+      hipLaunchKernelGGL(gemm_direct_pair_kernel<0>, grid, block, 0, st, a, n1, b, n2, dwf);
+    timing_after(st);
+  }
+  if (hipError_t e = hipGetLastError()) return e;
+  // both split sums and the v/b sums in one launch
+  return launch_splitk_reduce(gw.plan_splits > 1 ? split_sum_of(gw, gw.plan_splits) : SplitSum{},
+                              gx.plan_splits > 1 ? split_sum_of(gx, gx.plan_splits) : SplitSum{},
+                              gw.vb, st);
 }
 
 template <class S>

@@ -339,12 +339,12 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Workgroup w of a product's nwg.  smem: C::LDS bytes; row_signs: C::BM words
+// (fp32 products).
 template <class C, bool A_KC, bool B_KC, int MODE, class S>
-__global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
-  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
-
-  const TileIdx ti = tile_of(g);
+__device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
+                                            unsigned char* smem, unsigned* row_signs) {
+  const TileIdx ti = tile_of(g, w, nwg);
   const int m0 = ti.tm * C::BM;
   const int n0 = ti.tn * C::BN;
   const int kbeg = ti.split * g.k_per_split;
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g
     lds_only_barrier();
     unsigned any = 0;
 #pragma unroll
-    for (int w = 0; w < C::WAVES; ++w) any |= flag[w];
+    for (int i = 0; i < C::WAVES; ++i) any |= flag[i];
     if (__builtin_amdgcn_readfirstlane(any)) {
       clear();
       for (int kt = 0; kt < nk; ++kt) {
@@ -507,6 +507,26 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g
   if (g.add_count == 0) write_tile_add<C, 0>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
   else if (g.add_count == 1) write_tile_add<C, 1>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
   else write_tile_add<C, 2>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+}
+
+template <class C, bool A_KC, bool B_KC, int MODE, class S>
+__global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
+  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
+  staged_tile<C, A_KC, B_KC, MODE, S>(g, blockIdx.x, gridDim.x, smem, row_signs);
+}
+
+// dX (n1 workgroups; W row-contiguous in fp32, its transposed copy in bf16)
+// and dW (n2) in one launch, the one of longer workgroups first.
+template <class C, class S>
+__global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_pair_kernel(KernelArgs g1, int n1,
+                                                                         KernelArgs g2, int n2,
+                                                                         bool dw_first) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
+  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
+  const PairIdx p = pair_index(n1, n2, dw_first);
+  if (p.dx) staged_tile<C, true, sizeof(S) == 2, kChunk, S>(g1, p.w, n1, smem, row_signs);
+  else staged_tile<C, false, false, kChunk, S>(g2, p.w, n2, smem, row_signs);
 }
 
 // Tiles.  Big: 8 waves of 64 x 128, one workgroup per CU; fewest bytes and
@@ -557,39 +577,64 @@ struct Plan {
 // A K-contiguous product is split only where its 128 x 128 tiles fill at most
 // a quarter of the CUs: its other results do not depend on M, so that a
 // sequence cut into calls gives one call's bits.
-Plan plan_staged(const GemmDesc& g) {
-  Plan best{0, 1};
-  double best_cost = -1.0;
+struct SplitRange {
+  int lo, hi;
+};
+SplitRange split_range(const GemmDesc& g, int t) {
   const int mid_tiles = (int)std::min<long long>(
       ((g.M + 127LL) / 128) * ((g.N + 127LL) / 128), 1 << 20);
+  int lo = 1, hi = 1;
+  if (!g.a_kc && !g.bf16) {
+    lo = (g.K + 2047) / 2048;
+    if (t < 2) lo = std::max(lo, std::min({48, g.K / 128, (384 + mid_tiles - 1) / mid_tiles}));
+  }
+  if (!g.a_kc || (g.kc_split && mid_tiles <= 64))
+    hi = std::max(lo, std::min(64, (g.K + tile_cost(g, t).bk - 1) / tile_cost(g, t).bk / 4));
+  return {lo, hi};
+}
+// every count up to 6, then steps of a third or less
+int next_split(int s) { return s + std::max(1, s / 6); }
+
+// What a product is on tile t in s splits: workgroups, 16-k steps of each,
+// the time its partials' traffic takes.
+struct Shape {
+  long long wg;
+  double steps, traffic;
+};
+Shape shape_of(const GemmDesc& g, int t, int s) {
+  const TileCost& c = tile_cost(g, t);
+  const long long tiles = (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
+  const int kt = (g.K + c.bk - 1) / c.bk;
+  return {tiles * s, (double)((kt + s - 1) / s) * c.bk / 16,
+          s > 1 ? (2 * s + 1) * 4.0 * g.M * g.N / kBytesPerUs : 0.0};
+}
+// the real number of splits, each of whole K steps
+int real_splits(const GemmDesc& g, int t, int s) {
+  const int bk = tile_cost(g, t).bk, kt = (g.K + bk - 1) / bk, per = (kt + s - 1) / s;
+  return (kt + per - 1) / per;
+}
+
+Plan plan_staged(const GemmDesc& g, double* time = nullptr) {
+  if (g.plan_splits > 0) return {g.plan_tile, g.plan_splits};
+  Plan best{0, 1};
+  double best_cost = -1.0;
   for (int t = 0; t < 3; ++t) {
     const TileCost& c = tile_cost(g, t);
-    const long long tiles = (long long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
-    const int kt = (g.K + c.bk - 1) / c.bk;
-    int lo = 1, hi = 1;
-    if (!g.a_kc && !g.bf16) {
-      lo = (g.K + 2047) / 2048;
-      if (t < 2) lo = std::max(lo, std::min({48, g.K / 128, (384 + mid_tiles - 1) / mid_tiles}));
-    }
-    if (!g.a_kc || (g.kc_split && mid_tiles <= 64)) hi = std::max(lo, std::min(64, kt / 4));
-    // every count up to 6, then steps of a third or less
-    for (int s = lo; s <= hi; s += std::max(1, s / 6)) {
-      const long long per_cu = (tiles * s + 255) / 256;
-      const double steps = (double)((kt + s - 1) / s) * c.bk / 16;
-      double cost = per_cu == 1 ? c.base_alone + steps * c.alone
-                                : per_cu * (c.base_shared + steps * c.shared);
-      if (s > 1) cost += kSumLaunch + (2 * s + 1) * 4.0 * g.M * g.N / kBytesPerUs;
+    const SplitRange r = split_range(g, t);
+    for (int s = r.lo; s <= r.hi; s = next_split(s)) {
+      const Shape h = shape_of(g, t, s);
+      const long long per_cu = (h.wg + 255) / 256;
+      double cost = per_cu == 1 ? c.base_alone + h.steps * c.alone
+                                : per_cu * (c.base_shared + h.steps * c.shared);
+      if (s > 1) cost += kSumLaunch + h.traffic;
       if (best_cost < 0 || cost < best_cost) {
         best = {t, s};
         best_cost = cost;
       }
     }
   }
-  // the real number of splits, each of whole K steps
-  const int bk = tile_cost(g, best.tile).bk;
-  const int kt = (g.K + bk - 1) / bk;
-  const int per = (kt + best.splits - 1) / best.splits;
-  best.splits = (kt + per - 1) / per;
+  best.splits = real_splits(g, best.tile, best.splits);
+  if (time) *time = best_cost;
   return best;
 }
 
@@ -648,12 +693,7 @@ hipError_t launch_tile(int tile, const GemmDesc& g, const KernelArgs& a, hipStre
                      : launch_layout<FSmall<NP>>(g, a, st);
 }
 
-}  // namespace
-
-int gemm_staged_splits(const GemmDesc& g) { return plan_staged(g).splits; }
-
-hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
-  const Plan p = plan_staged(g);
+KernelArgs staged_args(const GemmDesc& g, const Plan& p) {
   const TileCost& c = tile_cost(g, p.tile);
   const int kt = (g.K + c.bk - 1) / c.bk;
   KernelArgs a{};
@@ -680,10 +720,79 @@ hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
     a.add_ld = g.add_ld;
     a.add_off = g.add_off;
   }
+  return a;
+}
+
+template <class C, class S>
+void launch_pair(const KernelArgs& ax, const KernelArgs& aw, hipStream_t st) {
+  const int n1 = ax.tiles_m * ax.tiles_n * ax.splits, n2 = aw.tiles_m * aw.tiles_n * aw.splits;
+  hipLaunchKernelGGL((gemm_staged_pair_kernel<C, S>), dim3(n1 + n2), dim3(C::THREADS), 0, st, ax,
+                     n1, aw, n2, aw.k_per_split > ax.k_per_split);
+}
+
+}  // namespace
+
+int gemm_staged_splits(const GemmDesc& g) { return plan_staged(g).splits; }
+
+hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
+  const Plan p = plan_staged(g);
+  const KernelArgs a = staged_args(g, p);
   timing_before(gemm_label(g), st);
   const hipError_t e = g.bf16 ? launch_tile<1>(p.tile, g, a, st) : launch_tile<3>(p.tile, g, a, st);
   timing_after(st);
   return e;
+}
+
+// Mid or Small tiles for both (Big ones fill the chip by themselves), where
+// pair_time beats the two plans one after the other.  L 64, B 32, d 256 fp32
+// (Small tiles): 21 us against 15 + 15.  Shapes
+// that fill the chip one by one gain nothing (L 400, B 32, 256 -> 128 units in
+// both directions, Mid: 106 us against 68 + 47, the step no faster).
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
+  GemmPair best{0, 0, 0};
+  if (gx.bf16 != gw.bf16 || gx.a_bf16 != gw.a_bf16 || !gx.a_kc || gx.b_kc != gx.a_bf16 ||
+      gw.a_kc || gw.b_kc || gx.a_bf16 != gx.bf16)
+    return best;
+  double tx, tw;
+  plan_staged(gx, &tx);
+  plan_staged(gw, &tw);
+  double best_cost = tx + tw;
+  for (int t = 1; t < 3; ++t) {
+    const TileCost& c = tile_cost(gx, t);
+    const SplitRange rx = split_range(gx, t), rw = split_range(gw, t);
+    for (int sx = rx.lo; sx <= rx.hi; sx = next_split(sx)) {
+      const Shape x = shape_of(gx, t, sx);
+      for (int sw = rw.lo; sw <= rw.hi; sw = next_split(sw)) {
+        const Shape w = shape_of(gw, t, sw);
+        const double cost =
+            c.base_alone +
+            pair_time(x.wg, x.steps, c.alone, w.wg, w.steps, c.alone, c.base_shared, c.shared) +
+            x.traffic + w.traffic + (sx > 1 || sw > 1 ? kSumLaunch : 0.0);
+        if (cost < best_cost) {
+          best = {t, real_splits(gx, t, sx), real_splits(gw, t, sw)};
+          best_cost = cost;
+        }
+      }
+    }
+  }
+  return best;
+}
+
+bool gemm_staged_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t st) {
+  const TileCost& c = tile_cost(gx, gx.plan_tile);
+  if (load_mode(gx, c.bm, c.bn, c.bk) != kChunk || load_mode(gw, c.bm, c.bn, c.bk) != kChunk)
+    return false;
+  const KernelArgs ax = staged_args(gx, plan_staged(gx)), aw = staged_args(gw, plan_staged(gw));
+  timing_before("gemm_dx_dw", st);
+  if (gx.bf16) {
+    if (gx.plan_tile == 1) launch_pair<FMid<1>, uint16_t>(ax, aw, st);
+    else launch_pair<FSmall<1>, uint16_t>(ax, aw, st);
+  } else {
+    if (gx.plan_tile == 1) launch_pair<FMid<3>, float>(ax, aw, st);
+    else launch_pair<FSmall<3>, float>(ax, aw, st);
+  }
+  timing_after(st);
+  return true;
 }
 
 }  // namespace sru

@@ -121,9 +121,8 @@ __device__ __forceinline__ void write_tile_add(const KernelArgs& g,
 struct TileIdx {
   int split, tm, tn;
 };
-__device__ __forceinline__ TileIdx tile_of(const KernelArgs& g) {
-  const int nwg = gridDim.x;
-  const int w = blockIdx.x;
+// w: the workgroup's index among the nwg of its product.
+__device__ __forceinline__ TileIdx tile_of(const KernelArgs& g, int w, int nwg) {
   const int q = nwg / 8, rmd = nwg % 8, x = w % 8;
   const int u = x * q + (x < rmd ? x : rmd) + w / 8;
   const int nt = g.tiles_m * g.tiles_n;
@@ -142,6 +141,33 @@ __device__ __forceinline__ TileIdx tile_of(const KernelArgs& g) {
   r.tm = first + tg % rows;
   r.tn = tg / rows;
   return r;
+}
+
+// Two products in one launch: workgroup p.w of the first (n1) or the second
+// (n2), which comes first where second_first.
+struct PairIdx {
+  bool dx;
+  int w;
+};
+__device__ __forceinline__ PairIdx pair_index(int n1, int n2, bool second_first) {
+  const int b = blockIdx.x;
+  const bool dx = second_first ? b >= n2 : b < n1;
+  return {dx, b - (dx == second_first ? (dx ? n2 : n1) : 0)};
+}
+
+// Time in us of n1 workgroups of s1 steps and n2 of s2 together, two slots per
+// CU: a1, a2 per step of one alone on its CU, `shared` (and `start` each) per
+// step of each of two.  Up to 256 workgroups the longest alone; up to 512 two
+// on some CU, the longer of which ends alone; beyond, all steps over the CUs
+// and about a third of a long workgroup's time as the tail.
+inline double pair_time(long long n1, double s1, double a1, long long n2, double s2, double a2,
+                        double start, double shared) {
+  const double longest = s1 > s2 ? s1 : s2, least = s1 > s2 ? s2 : s1;
+  if (n1 + n2 <= 256) return s1 * a1 > s2 * a2 ? s1 * a1 : s2 * a2;
+  if (n1 + n2 <= 512)
+    return 2 * (start + shared * least) + (longest - least) * (s1 > s2 ? a1 : a2);
+  return (n1 * (start + shared * s1) + n2 * (start + shared * s2)) / 256.0 +
+         0.6 * shared * longest;
 }
 
 }  // namespace

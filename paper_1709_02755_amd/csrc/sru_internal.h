@@ -79,6 +79,8 @@ struct GemmDesc {
   // (on its own when this product is not split).
   bool defer_sum;
   SplitSum extra;
+  // a plan made elsewhere (gemm_pair_plan): splits, 0 = gemm_launch plans
+  int plan_tile, plan_splits;
 };
 
 // The split sum gemm_launch would run after g (its partials, split count,
@@ -104,10 +106,24 @@ int gemm_splits(const GemmDesc& g);
 bool gemm_is_direct(const GemmDesc& g);
 size_t gemm_partial_bytes(int M, int N, int splits);
 hipError_t gemm_launch(const GemmDesc& g, hipStream_t stream);
+// Two products that do not depend on each other (dX and dW of one dU) in one
+// launch, where their tiles together are modelled faster than one after the
+// other: each then fills the CUs the other leaves idle.  splits_x is 0 where
+// they are not paired.  Depends on the sizes and layouts only.
+struct GemmPair {
+  int tile, splits_x, splits_w;
+};
+GemmPair gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gw);
+// Runs both products (planned as pair: plan_tile and plan_splits set) and
+// their split sums.
+hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t stream);
 // The products staged through registers (sru_gemm_staged.hip): the split
 // count, and the product itself without its split sum.
 int gemm_staged_splits(const GemmDesc& g);
 hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t stream);
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw);
+// false where the operands' alignment needs other loads (nothing is enqueued)
+bool gemm_staged_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t stream);
 // Name of a product for the measurement hook.
 inline const char* gemm_label(const GemmDesc& g) {
   return g.label ? g.label : !g.b_kc ? (g.a_kc ? "gemm_nn" : "gemm_tn") : "gemm_nt";
