@@ -1390,6 +1390,180 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_tp_kernel(ScanS
   }
 }
 
+// --------------------------------------- gated backward, few lanes
+// Below kTpMinLanes the reverse scan keeps the order of the sequential one
+// (its results do not depend on how a sequence is cut into calls).  There a
+// step of scan_bwd_kernel takes 165-250 ns: one wave issues its 45
+// instructions and waits for its loads.  But only two or three of them lie
+// between one carried gradient and the next.  So a workgroup of 32 lanes
+// works on a block of NW chunks of CH steps, each half wave on one:
+//   1. every chunk computes what does not depend on the carried gradient
+//      (gates, dr, the factors of the chain), all at once, and loads the next
+//      block's inputs;
+//   2. the chunks carry the gradient through their steps one after the other
+//      (two or three dependent operations a step), handing it over in LDS;
+//   3. every chunk computes the rest and stores.
+// The operations on every value are scan_bwd_kernel's, so dU, dx_hat and dc0
+// are the same bits; the v/b sums over t are added up per chunk, then over
+// the chunks in a fixed order.  Bound by 2. at few lanes: about 0.12 us per
+// chunk.  Sequential -> this, with the sum over b: L 77, B 8, d 300
+// bidirectional masked 19.4 -> 13.3 us; L 256, B 1, d 1024 42.4 -> 17.4 us;
+// L 400, B 4, d 128 bidirectional masked 70.3 -> 25.7 us; L 2000, B 2, d 512
+// 296 -> 98.5 us.
+template <int KB, bool MASK, bool DUB, bool RN, int CH>
+__global__ __launch_bounds__(32 * kLinMaxWaves) void scan_bwd_few_kernel(ScanShape s,
+                                                                         ScanBwdArgs a) {
+  constexpr int LW = 32;
+  __shared__ float carry[LW];
+  __shared__ float4 sums[kLinMaxWaves][LW];
+  Lane ln;
+  const bool live = decode_lane_lin<LW>(s, ln, blockIdx.x);
+  const int lane = threadIdx.x & (LW - 1);
+  const int w = threadIdx.x / LW;
+  const int NW = blockDim.x / LW;
+  const int L = s.L;
+  const int d = s.d;
+  const long long nfeat = (long long)s.ndir * s.d;
+  const long long u_step = (long long)s.B * s.ndir * KB * s.d;
+  const long long x_step = (long long)s.B * s.d_in;
+  const long long h_step = (long long)s.B * nfeat;
+  const long long u_off = ((long long)ln.b * s.ndir + ln.dir) * KB * s.d + ln.j;
+  const float* up = a.U + u_off;
+  using DuT = typename std::conditional<DUB, uint16_t, float>::type;
+  DuT* dup = static_cast<DuT*>(a.dU) + u_off;
+  const float* xp = KB == 3 ? a.X + (long long)ln.b * s.d_in + ln.j : nullptr;
+  const uint8_t* mp = MASK ? a.mask + ln.b : nullptr;
+  const float* cpp = a.C + ln.gid;
+  const float* dhp = a.dH + ln.gid;
+  const float vf = a.v_f[ln.fidx], vr = a.v_r[ln.fidx];
+  const float vfs = vf * kNegLog2e, vrs = vr * kNegLog2e;
+  const float bfs = a.b_f[ln.fidx] * kNegLog2e, brs = a.b_r[ln.fidx] * kNegLog2e;
+  const float alpha = s.alpha;
+  const float c0v = a.c0 ? a.c0[ln.gid] : 0.0f;
+  float sum_df_c = 0.f, sum_dr_c = 0.f, sum_df = 0.f, sum_dr = 0.f;
+  // time index of processing index i (reverse of the direction's order;
+  // clamped into range)
+  auto tproc = [&](int i) {
+    const int pos = L - 1 - (i < L ? i : L - 1);
+    return (long long)(ln.rev ? L - 1 - pos : pos);
+  };
+
+  float ru0[CH], ru1[CH], ru2[CH], rx[CH], rdh[CH], rc[CH + 1];
+  unsigned rm[CH];
+  (void)rm;
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int m = 0; m < CH; ++m) {
+      const long long t = tproc(i0 + m);
+      const float* u = up + t * u_step;
+      ru0[m] = __builtin_nontemporal_load(u);
+      ru1[m] = __builtin_nontemporal_load(u + d);
+      ru2[m] = __builtin_nontemporal_load(u + 2 * d);
+      if constexpr (KB == 4) rx[m] = __builtin_nontemporal_load(u + 3 * d);
+      else rx[m] = xp[t * x_step];
+      rdh[m] = __builtin_nontemporal_load(dhp + t * h_step);
+      rc[m] = cpp[t * h_step];
+      if constexpr (MASK) rm[m] = mp[t * s.B];
+    }
+    const int ie = i0 + CH;  // c_{t-1} of the chunk's last step
+    rc[CH] = ie < L ? cpp[tproc(ie) * h_step] : c0v;
+  };
+
+  if (w == 0) carry[lane] = a.dc_last ? a.dc_last[ln.gid] : 0.0f;
+  load(w * CH);
+  for (int base = 0; base < L; base += NW * CH) {
+    const int i0 = base + w * CH;
+    const int nv = min(CH, L - i0);  // this chunk's steps (none: <= 0)
+    // 1. everything but the carried gradient
+    float r[CH], dh[CH], gf[CH], dr[CH], pf[CH], omf[CH], dx[CH], cp[CH], cr[CH], gc[CH];
+    bool pad[CH];
+#pragma unroll
+    for (int m = 0; m < CH; ++m) {
+      const float c_t = rc[m];
+      cp[m] = i0 + m + 1 < L ? rc[m + 1] : c0v;
+      cr[m] = RN ? c_t : cp[m];
+      const float f = sigmoid_scaled(fmaf(vfs, cp[m], fmaf(ru1[m], kNegLog2e, bfs)));
+      r[m] = sigmoid_scaled(fmaf(vrs, cr[m], fmaf(ru2[m], kNegLog2e, brs)));
+      pad[m] = MASK && rm[m] != 0;
+      dh[m] = pad[m] ? 0.0f : rdh[m];
+      const float rr = r[m] * (1.0f - r[m]);
+      const float ff = f * (1.0f - f);
+      dr[m] = dh[m] * (c_t - alpha * rx[m]) * rr;
+      pf[m] = (cp[m] - ru0[m]) * ff;
+      omf[m] = 1.0f - f;
+      dx[m] = dh[m] * (1.0f - r[m]) * alpha;
+      if constexpr (MASK) {
+        dr[m] = pad[m] ? 0.0f : dr[m];
+        dx[m] = pad[m] ? 0.0f : dx[m];
+      }
+      gf[m] = fmaf(pf[m], vf, f);
+    }
+    if (base + NW * CH < L) load(i0 + NW * CH);
+    // 2. the carried gradient, chunk after chunk
+    for (int q = 0; q < NW; ++q) {
+      lds_barrier();
+      if (w == q) {
+        float g = carry[lane];
+#pragma unroll
+        for (int m = 0; m < CH; ++m) {
+          gc[m] = RN ? fmaf(dr[m], vr, fmaf(dh[m], r[m], g)) : fmaf(dh[m], r[m], g);
+          const float gn = RN ? gc[m] * gf[m] : fmaf(gc[m], gf[m], dr[m] * vr);
+          g = pad[m] || m >= nv ? g : gn;
+        }
+        carry[lane] = g;
+      }
+    }
+    // 3. the rest
+#pragma unroll
+    for (int m = 0; m < CH; ++m) {
+      if (m >= nv) break;
+      const long long t = tproc(i0 + m);
+      float df = gc[m] * pf[m];
+      float du0 = gc[m] * omf[m];
+      if constexpr (MASK) {
+        df = pad[m] ? 0.0f : df;
+        du0 = pad[m] ? 0.0f : du0;
+      }
+      sum_df_c = fmaf(df, cp[m], sum_df_c);
+      sum_dr_c = fmaf(dr[m], cr[m], sum_dr_c);
+      sum_df += df;
+      sum_dr += dr[m];
+      if (live) {
+        DuT* du = dup + t * u_step;
+        // bf16 dU through the cache, as in scan_bwd_kernel
+        auto put = [](float v, DuT* q) {
+          if constexpr (DUB) *q = __builtin_bit_cast(uint16_t, (__bf16)v);
+          else __builtin_nontemporal_store(v, q);
+        };
+        put(du0, du);
+        put(df, du + d);
+        put(dr[m], du + 2 * d);
+        if constexpr (KB == 4) put(dx[m], du + 3 * d);
+        else __builtin_nontemporal_store(dx[m], a.dxh + ln.gid + t * h_step);
+      }
+    }
+  }
+  sums[w][lane] = make_float4(sum_df_c, sum_dr_c, sum_df, sum_dr);
+  lds_barrier();
+  if (w == 0 && live) {
+    float4 t = sums[0][lane];
+    for (int m = 1; m < NW; ++m) {
+      const float4 q = sums[m][lane];
+      t.x += q.x;
+      t.y += q.y;
+      t.z += q.z;
+      t.w += q.w;
+    }
+    // one row of partials per sequence, as scan_bwd_kernel writes
+    float* part = a.partial + (long long)ln.b * 4 * nfeat + ln.fidx;
+    part[0] = t.x;
+    part[nfeat] = t.y;
+    part[2 * nfeat] = t.z;
+    part[3 * nfeat] = t.w;
+    if (a.dc0) a.dc0[ln.gid] = carry[lane];
+  }
+}
+
 // Sum of the per-sequence partials over b, in a fixed order (deterministic):
 // vb_sum_block, 64 outputs per workgroup of 4 waves.  The loads of a lane
 // are independent, so a launch costs about one memory round trip.  The same
@@ -1581,10 +1755,15 @@ hipError_t fwd_dispatch_c(const ScanShape& s, const ScanFwdArgs& a, hipStream_t 
 // sequence without segments), and fewer lanes than half the SIMDs hold a
 // wave each.  Measured at L 256, d 1024: 16,384 lanes 35.5 us against 48.5
 // us sequential; 32,768 lanes 62.2 against 56.8 us (and sequential ahead up
-// to 61,440 lanes).  Smaller shapes keep the sequential scan, whose results
-// do not depend on how a sequence is cut into calls.
+// to 61,440 lanes).  Smaller shapes keep the sequential scan's results, which
+// do not depend on how a sequence is cut into calls: in chunks
+// (scan_bwd_few_kernel) past kFewMinLen steps, and up to there in
+// scan_bwd_kernel, which has no chunks to start (with the sum over b: L 4,
+// B 4, d 1024 5.1 us against 6.4; L 16, B 7 7.6 against 7.5; L 32, B 4, d 128
+// 9.9 against 7.0).
 constexpr long long kTpMinLanes = 128 * 64;
 constexpr long long kTpMaxLanes = 32768;  // exclusive
+constexpr int kFewMinLen = 16;            // exclusive
 bool bwd_tp_ok(const ScanShape& s) {
   const long long lanes = (long long)s.B * s.ndir * s.d;
   return !s.linear && lanes >= kTpMinLanes && lanes < kTpMaxLanes &&
@@ -1632,6 +1811,22 @@ void bwd_tp_launch(const ScanShape& s, const ScanBwdArgs& a, const LinPlan& pl, 
 }
 
 template <int KB, bool MASK>
+void bwd_few_launch(const ScanShape& s, const ScanBwdArgs& a, int lanes, hipStream_t st) {
+  // as many chunks as the sequence has, at most 16 (whole waves of two)
+  int nw = 2;
+  while (nw < kLinMaxWaves && nw * kBwdTpCH < s.L) nw *= 2;
+  const dim3 g((lanes + 31) / 32), b(32 * nw);
+  if (a.du_bf16 && s.reset_new)
+    hipLaunchKernelGGL((scan_bwd_few_kernel<KB, MASK, true, true, kBwdTpCH>), g, b, 0, st, s, a);
+  else if (a.du_bf16)
+    hipLaunchKernelGGL((scan_bwd_few_kernel<KB, MASK, true, false, kBwdTpCH>), g, b, 0, st, s, a);
+  else if (s.reset_new)
+    hipLaunchKernelGGL((scan_bwd_few_kernel<KB, MASK, false, true, kBwdTpCH>), g, b, 0, st, s, a);
+  else
+    hipLaunchKernelGGL((scan_bwd_few_kernel<KB, MASK, false, false, kBwdTpCH>), g, b, 0, st, s, a);
+}
+
+template <int KB, bool MASK>
 hipError_t bwd_dispatch(const ScanShape& s, const ScanBwdArgs& a, hipStream_t st) {
   const int lanes = s.B * s.ndir * s.d;
   const int grid = (lanes + kScanThreads - 1) / kScanThreads;
@@ -1660,7 +1855,8 @@ hipError_t bwd_dispatch(const ScanShape& s, const ScanBwdArgs& a, hipStream_t st
     return hipGetLastError();
   }
   timing_before("scan_bwd", st);
-  if (lanes >= kFullLanes) bwd_launch<KB, MASK, kBwdPFFull>(s, a, grid, st);
+  if (lanes < kTpMinLanes && s.L > kFewMinLen) bwd_few_launch<KB, MASK>(s, a, lanes, st);
+  else if (lanes >= kFullLanes) bwd_launch<KB, MASK, kBwdPFFull>(s, a, grid, st);
   else bwd_launch<KB, MASK, kBwdPF>(s, a, grid, st);
   timing_after(st);
   return hipGetLastError();
