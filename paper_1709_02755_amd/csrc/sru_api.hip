@@ -225,22 +225,23 @@ struct BwdLayout {
   size_t dU, dxh, partial, wt, xb, splitk, splitk_dx, total;
   int splits, splits_dx;
   bool joint_sum;
-  sru::GemmPair pair;  // dX and dW in one launch (splits_x > 0)
+  sru::GemmPairPlan pair;  // dX and dW in one launch (splits_x > 0)
 };
 
-// dX = dU Wcat (+ highway): NN on Wcat in fp32 mode; in bf16 mode NT on the
-// bf16 Wcat^T.  Its tiles can be too few to fill the CUs (d_in of a few
+// dX = dU Wcat (+ highway): NN on Wcat in fp32 mode, and in bf16 mode where
+// the pair with dW asks for it (nn; wt is then Wcat rounded); else in bf16
+// mode NT on the bf16 Wcat^T.  Its tiles can be too few to fill the CUs (d_in of a few
 // hundred, or few tokens: one GPU's share of a batch), so it may be split
 // over K; the launcher's plan decides.
 // With k = 3 the product adds every direction's highway gradient dxh.  The
 // addend is part of the descriptor the workspace is sized from, since it
 // decides the tile shape and with it the split count.
 sru::GemmDesc dx_desc(const Dims& s, bool bf16, const void* dU, const void* W, const void* wt,
-                      float* dX, const float* dxh) {
-  sru::GemmDesc g = bf16 ? gemm_desc(SRU_OP_NT, true, (int)s.M, s.d_in, (int)s.N, dU, s.N, wt,
+                      float* dX, const float* dxh, bool nn) {
+  sru::GemmDesc g = bf16 && !nn ? gemm_desc(SRU_OP_NT, true, (int)s.M, s.d_in, (int)s.N, dU, s.N, wt,
                                      s.N, dX, s.d_in)
-                         : gemm_desc(SRU_OP_NN, false, (int)s.M, s.d_in, (int)s.N, dU, s.N, W,
-                                     s.d_in, dX, s.d_in);
+                         : gemm_desc(SRU_OP_NN, bf16, (int)s.M, s.d_in, (int)s.N, dU, s.N,
+                                     bf16 ? wt : W, s.d_in, dX, s.d_in);
   g.a_bf16 = g.b_bf16 = bf16;
   g.kc_split = true;
   g.label = "gemm_dx";
@@ -268,8 +269,10 @@ BwdLayout bwd_layout(const Dims& s, int gemm_dtype) {
   w.xb = off;
   if (bf16) off += align_up(2 * (size_t)s.M * (size_t)s.d_in);
   const sru::GemmDesc gw = dw_desc(s, bf16, nullptr, nullptr, nullptr);
-  const sru::GemmDesc gx = dx_desc(s, bf16, nullptr, nullptr, nullptr, nullptr, nullptr);
-  if (!dx_last(s)) w.pair = sru::gemm_pair_plan(gx, gw);
+  const sru::GemmDesc gx = dx_desc(s, bf16, nullptr, nullptr, nullptr, nullptr, nullptr, false);
+  if (!dx_last(s))
+    w.pair = sru::gemm_pair_plan(
+        gx, dx_desc(s, bf16, nullptr, nullptr, nullptr, nullptr, nullptr, true), gw);
   const bool paired = w.pair.splits_x > 0;
   w.splits = paired ? w.pair.splits_w : sru::gemm_splits(gw);
   w.splits_dx = paired ? w.pair.splits_x : sru::gemm_splits(gx);
@@ -669,7 +672,8 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
     if (int e = round_x()) return e;
     return hip_status(sru::gemm_launch(gw, stream));
   };
-  sru::GemmDesc gx = dx_desc(s, bf16, dU, W, wt, dX, dxh);
+  const bool nn = paired && lay.pair.nn;
+  sru::GemmDesc gx = dx_desc(s, bf16, dU, W, nn && W_bf16 ? W_bf16 : wt, dX, dxh, nn);
   gx.partials = reinterpret_cast<float*>(ws + lay.splitk_dx);
   if (paired) {
     gx.plan_tile = lay.pair.tile;
@@ -693,7 +697,13 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
     return hip_status(sru::gemm_launch(gx, stream));
   };
   if (paired) {
-    if (int e = transpose_w()) return e;
+    if (!nn) {
+      if (int e = transpose_w()) return e;
+    } else if (bf16 && !W_bf16) {
+      if (int e = hip_status(
+              sru::to_bf16_launch(W, (int)s.N, d_in, wt, false, stream, "bf16_w")))
+        return e;
+    }
     if (int e = round_x()) return e;
     return hip_status(sru::gemm_pair_launch(gx, gw, stream));
   }

@@ -516,8 +516,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g
   staged_tile<C, A_KC, B_KC, MODE, S>(g, blockIdx.x, gridDim.x, smem, row_signs);
 }
 
-// dX (n1 workgroups; W row-contiguous in fp32, its transposed copy in bf16)
-// and dW (n2) in one launch, the one of longer workgroups first.
+// dX (n1 workgroups; W read as it lies, row-contiguous, so bf16 needs no
+// transposed copy) and dW (n2) in one launch, the one of longer workgroups
+// first.
 template <class C, class S>
 __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_pair_kernel(KernelArgs g1, int n1,
                                                                          KernelArgs g2, int n2,
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_pair_kernel(KernelA
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
   __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
   const PairIdx p = pair_index(n1, n2, dw_first);
-  if (p.dx) staged_tile<C, true, sizeof(S) == 2, kChunk, S>(g1, p.w, n1, smem, row_signs);
+  if (p.dx) staged_tile<C, true, false, kChunk, S>(g1, p.w, n1, smem, row_signs);
   else staged_tile<C, false, false, kChunk, S>(g2, p.w, n2, smem, row_signs);
 }
 
@@ -734,6 +735,12 @@ void launch_pair(const KernelArgs& ax, const KernelArgs& aw, hipStream_t st) {
 
 int gemm_staged_splits(const GemmDesc& g) { return plan_staged(g).splits; }
 
+double gemm_staged_time(const GemmDesc& g) {
+  double t;
+  plan_staged(g, &t);
+  return t;
+}
+
 hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
   const Plan p = plan_staged(g);
   const KernelArgs a = staged_args(g, p);
@@ -743,22 +750,26 @@ hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t st) {
   return e;
 }
 
+// The pair is built for chunk loads: by the sizes here, by the pointers too at
+// the launch.
+static bool pair_loads(const GemmDesc& gx, const GemmDesc& gw, const TileCost& c) {
+  return load_mode(gx, c.bm, c.bn, c.bk) == kChunk && load_mode(gw, c.bm, c.bn, c.bk) == kChunk;
+}
+
 // Mid or Small tiles for both (Big ones fill the chip by themselves), where
 // pair_time beats the two plans one after the other.  L 64, B 32, d 256 fp32
 // (Small tiles): 21 us against 15 + 15.  Shapes
 // that fill the chip one by one gain nothing (L 400, B 32, 256 -> 128 units in
 // both directions, Mid: 106 us against 68 + 47, the step no faster).
-GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double tx) {
   GemmPair best{0, 0, 0};
-  if (gx.bf16 != gw.bf16 || gx.a_bf16 != gw.a_bf16 || !gx.a_kc || gx.b_kc != gx.a_bf16 ||
-      gw.a_kc || gw.b_kc || gx.a_bf16 != gx.bf16)
+  if (gx.bf16 != gw.bf16 || gx.a_bf16 != gw.a_bf16 || !gx.a_kc || gx.b_kc || gw.a_kc || gw.b_kc ||
+      gx.a_bf16 != gx.bf16)
     return best;
-  double tx, tw;
-  plan_staged(gx, &tx);
-  plan_staged(gw, &tw);
-  double best_cost = tx + tw;
+  double best_cost = tx + gemm_staged_time(gw);
   for (int t = 1; t < 3; ++t) {
     const TileCost& c = tile_cost(gx, t);
+    if (!pair_loads(gx, gw, c)) continue;
     const SplitRange rx = split_range(gx, t), rw = split_range(gw, t);
     for (int sx = rx.lo; sx <= rx.hi; sx = next_split(sx)) {
       const Shape x = shape_of(gx, t, sx);
@@ -780,8 +791,7 @@ GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
 
 bool gemm_staged_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t st) {
   const TileCost& c = tile_cost(gx, gx.plan_tile);
-  if (load_mode(gx, c.bm, c.bn, c.bk) != kChunk || load_mode(gw, c.bm, c.bn, c.bk) != kChunk)
-    return false;
+  if (!pair_loads(gx, gw, c)) return false;
   const KernelArgs ax = staged_args(gx, plan_staged(gx)), aw = staged_args(gw, plan_staged(gw));
   timing_before("gemm_dx_dw", st);
   if (gx.bf16) {

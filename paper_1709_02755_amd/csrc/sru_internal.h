@@ -113,7 +113,12 @@ hipError_t gemm_launch(const GemmDesc& g, hipStream_t stream);
 struct GemmPair {
   int tile, splits_x, splits_w;
 };
-GemmPair gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gw);
+// gx_nn: the same dX with W as it lies (row-contiguous), which the staged pair
+// reads; in bf16 gx reads W's transposed copy.
+struct GemmPairPlan : GemmPair {
+  bool nn;  // run as gx_nn
+};
+GemmPairPlan gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gx_nn, const GemmDesc& gw);
 // Runs both products (planned as pair: plan_tile and plan_splits set) and
 // their split sums.
 hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t stream);
@@ -121,7 +126,9 @@ hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t 
 // count, and the product itself without its split sum.
 int gemm_staged_splits(const GemmDesc& g);
 hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t stream);
-GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw);
+double gemm_staged_time(const GemmDesc& g);  // modelled, us
+// tx: the time of dX by itself
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double tx);
 // false where the operands' alignment needs other loads (nothing is enqueued)
 bool gemm_staged_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t stream);
 // Name of a product for the measurement hook.

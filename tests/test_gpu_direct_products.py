@@ -1,4 +1,5 @@
-"""The layer's bf16 products (both tile sizes, split and whole) against float64
+"""The layer's bf16 products (both tile sizes, split and whole, and the
+staged pair of dX and dW) against float64
 products of the same bf16-rounded operands: U, dX with its addends, dW.
 
 Bound per element: an fp32 chain of K products in 16-k slabs, each rounded at
@@ -22,6 +23,12 @@ CASES = [
     (256, 8, 1024, 1024, sru.DIR_FWD),    # one GPU's shard: dW and dX split, one sum
     (130, 33, 1032, 520, sru.DIR_FWD),    # ragged edges over many tiles
     (128, 64, 1024, 1024, sru.DIR_FWD),   # big tiles
+    # dX with dW on staged tiles, W as it lies: rows of whole 8-byte chunks only
+    (77, 13, 300, 200, sru.DIR_BI),       # dX alone would run direct
+    (9, 5, 76, 36, sru.DIR_FWD),          # less than one tile of tokens
+    (33, 9, 100, 100, sru.DIR_REV),       # one addend, N no whole 16-byte chunks
+    (61, 19, 84, 84, sru.DIR_BI),         # two addends
+    (25, 4, 77, 52, sru.DIR_FWD),         # rows in single elements: not paired
 ]
 
 
@@ -45,6 +52,11 @@ def test_layer_products(case):
     kw = dict(direction=direction)
     fw = sru.forward(X, W, *p, gemm_dtype=sru.GEMM_BF16, **kw)
     bw = sru.backward(X, W, *p, fw["U"], fw["C"], dH, gemm_dtype=sru.GEMM_BF16, **kw)
+    # the caller's rounded copies instead of the workspace's: the same bits
+    bc = sru.backward(X, W, *p, fw["U"], fw["C"], dH, gemm_dtype=sru.GEMM_BF16,
+                      X_bf16=X.bfloat16(), W_bf16=W.bfloat16(), **kw)
+    for n in ("dX", "dW"):
+        assert torch.equal(bc[n], bw[n]), n
     sc = sru.scan_backward(fw["U"], X, fw["C"], dH, *p, d_in=d_in, **kw)
     torch.cuda.synchronize()
     r64 = lambda t, *s: t.bfloat16().double().reshape(*s)
