@@ -1011,6 +1011,9 @@ __global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ 
 }
 
 // Transposed: dst[c*rows + r] = bf16(src[r*cols + c]) through a 64x64 LDS tile.
+// Few workgroups at the sizes it meets, so bound by latency: a thread's 16
+// loads are all in flight before the first is used (1600 x 300: 8.6 us one by
+// one, 4.6 so).  Rows and columns past the edge load the last one's.
 // Source element as fp32: fp32 as is, bf16 (raw bits) widened exactly.
 __device__ __forceinline__ float src_f32(float v) { return v; }
 __device__ __forceinline__ float src_f32(uint16_t v) {
@@ -1023,11 +1026,16 @@ __global__ __launch_bounds__(256) void to_bf16_t_kernel(const S* __restrict__ sr
   __shared__ float tile[64][65];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    tile[i][tx] = (r < rows && c < cols) ? src_f32(src[(long long)r * cols + c]) : 0.f;
+  S v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int r = min(r0 + ty + 4 * k, rows - 1), c = min(c0 + tx, cols - 1);
+    v[k] = src[(long long)r * cols + c];
   }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) tile[ty + 4 * k][tx] = src_f32(v[k]);
   __syncthreads();
+#pragma unroll
   for (int i = ty; i < 64; i += 4) {
     const int c = c0 + i, r = r0 + tx;
     if (c < cols && r < rows)
