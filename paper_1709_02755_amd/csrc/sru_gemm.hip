@@ -1204,12 +1204,12 @@ DirectPlan plan_direct(const GemmDesc& g, double* time = nullptr) {
 // after the other.  L 256, B 8, d 1024: dX in 2 splits
 // and dW whole, 40 us and 6 for the sum, against 21 + 21 us and 12 (each in 2
 // splits).
-GemmPair direct_pair_plan(const GemmDesc& gx, const GemmDesc& gw) {
+GemmPair direct_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double& best_cost) {
   GemmPair best{0, 0, 0};
   double tx, tw;
   plan_direct(gx, &tx);
   plan_direct(gw, &tw);
-  double best_cost = tx + tw;
+  best_cost = tx + tw;
   const int kx = (gx.K + 63) / 64, kw = (gw.K + 63) / 64;
   const DirectRange rx = direct_range(gx), rw = direct_range(gw);
   const long long nx = direct_tiles(gx, 128), nw = direct_tiles(gw, 128);
@@ -1343,19 +1343,29 @@ hipError_t gemm_launch(const GemmDesc& g, hipStream_t st) {
 // where that beats the two: L 77, B 13, 300 -> 200 units in both directions,
 // 18 us against 8.6 for W^T, 13.5 and 16.6 us and one more split sum (the whole
 // backward 54.2 -> 33.6 us); 20,000 tokens of 612 columns are left as they were.
+// Two that could run direct do so too at the smallest sizes, whose 64 x 64 tiles
+// are several where 128 x 128 is one: the backward of L 20, B 4, d 64 27.0 ->
+// 13.1 us, L 32, B 4, d 96 30.3 -> 15.2 us; from L 64, B 32, d 256 the direct
+// plans stay ahead.
 GemmPairPlan gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gx_nn, const GemmDesc& gw) {
   const bool dx = direct_ok(gx), dw = direct_ok(gw);
   if (gx.Cb || gw.Cb || gw.add_count != 0 || (dw && !dx)) return {};
-  if (dw) return {direct_pair_plan(gx, gw), false};
-  double tx;
-  if (dx) plan_direct(gx, &tx);
-  else tx = gemm_staged_time(gx);
-  return {gemm_staged_pair_plan(gx_nn, gw, tx), true};
+  GemmPairPlan p{};
+  double time;  // to beat
+  if (dw) {
+    static_cast<GemmPair&>(p) = direct_pair_plan(gx, gw, time);
+  } else {
+    if (dx) plan_direct(gx, &time);
+    else time = gemm_staged_time(gx);
+    time += gemm_staged_time(gw);
+  }
+  const GemmPair staged = gemm_staged_pair_plan(gx_nn, gw, time);
+  return staged.splits_x > 0 ? GemmPairPlan{staged, true} : p;
 }
 
 hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t st) {
-  const bool dx = direct_ok(gx);
-  if (dx != direct_ok(gw) || (!dx && !gemm_staged_pair_launch(gx, gw, st))) {
+  const bool dx = direct_ok(gx) && direct_ok(gw);
+  if (!dx && (gx.b_kc || !gemm_staged_pair_launch(gx, gw, st))) {
     // operands that need other loads than the plan assumed
     if (hipError_t e = gemm_launch(gx, st)) return e;
     return gemm_launch(gw, st);

@@ -761,12 +761,12 @@ static bool pair_loads(const GemmDesc& gx, const GemmDesc& gw, const TileCost& c
 // (Small tiles): 21 us against 15 + 15.  Shapes
 // that fill the chip one by one gain nothing (L 400, B 32, 256 -> 128 units in
 // both directions, Mid: 106 us against 68 + 47, the step no faster).
-GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double tx) {
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double time) {
   GemmPair best{0, 0, 0};
   if (gx.bf16 != gw.bf16 || gx.a_bf16 != gw.a_bf16 || !gx.a_kc || gx.b_kc || gw.a_kc || gw.b_kc ||
       gx.a_bf16 != gx.bf16)
     return best;
-  double best_cost = tx + gemm_staged_time(gw);
+  double best_cost = time;
   for (int t = 1; t < 3; ++t) {
     const TileCost& c = tile_cost(gx, t);
     if (!pair_loads(gx, gw, c)) continue;

@@ -127,8 +127,8 @@ hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t 
 int gemm_staged_splits(const GemmDesc& g);
 hipError_t gemm_staged_launch(const GemmDesc& g, hipStream_t stream);
 double gemm_staged_time(const GemmDesc& g);  // modelled, us
-// tx: the time of dX by itself
-GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double tx);
+// time: what the pair has to beat
+GemmPair gemm_staged_pair_plan(const GemmDesc& gx, const GemmDesc& gw, double time);
 // false where the operands' alignment needs other loads (nothing is enqueued)
 bool gemm_staged_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t stream);
 // Name of a product for the measurement hook.
