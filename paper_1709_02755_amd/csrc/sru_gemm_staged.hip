@@ -41,14 +41,20 @@
 // 3072 x 1024 over 16384 tokens 940 -> 557 us with its split sum, 2048 x 768
 // x 256 24.7 -> 13.1 us.
 //
-// Values below 2^-110 (8e-34) have parts below bf16's smallest (2^-133) and
-// keep an absolute error of that size.
+// Every fp32 value is a multiple of 2^-149, but bf16's smallest is 2^-133 and
+// its smallest normal value 2^-126: below 2^-110 the parts would lose bits
+// (2.7e-3 of a product of values around 1e-38).  So both operands are
+// multiplied by 2^24, which makes every part a normal number, and the results
+// by 2^-48, both exact but for results below 2^-126, which round once.  (The
+// row's sign rides on A's factor; the multiplication costs 0 to 3 % of a
+// product: 16384 x 3072 x 1024 467 us with and without, 4096 x 3072 x 1024
+// 147 -> 150 us.)
 //
-// A value whose bf16 rounding is not finite (infinities, NaN, magnitudes
-// above 3.39e38) turns its second part, and so every result it enters, into
-// NaN.  A workgroup that finds a result that is not finite therefore runs
-// its tile again with the fp32 matrix instruction: such results are fp32
-// arithmetic's own.
+// A value that is not finite after this (infinities, NaN, magnitudes above
+// 2^103 = 1e31) turns its second part, and so every result it enters, into
+// NaN, and results above 2^79 may overflow.  A workgroup that finds a result
+// that is not finite therefore runs its tile again with the fp32 matrix
+// instruction: such results are fp32 arithmetic's own.
 #include <algorithm>
 
 #include "sru_gemm_tile.h"
@@ -80,22 +86,21 @@ struct FCfg {
   static_assert(LDS <= 160 * 1024 && BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile");
 };
 
-// Sign bit of row r of a row-contiguous A: the Thue-Morse sequence.
-__device__ __forceinline__ unsigned row_sign(unsigned r) {
-  return (unsigned)__builtin_popcount(r) << 31;
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;  // factors of the operands, the results
+
+// x, negated where r has an odd number of bits.  Row r of a row-contiguous A:
+// the Thue-Morse sequence.
+__device__ __forceinline__ float signed_by(float x, unsigned r) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) ^
+                                       ((unsigned)__builtin_popcount(r) << 31));
 }
 
-__device__ __forceinline__ float flip(float x, unsigned sign) {
-  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) ^ sign);
-}
-
-// Two values' parts, packed per plane.  SIGN: of the values with their signs
-// flipped by sg.
-template <bool SIGN, int NP>
-__device__ __forceinline__ void split_pair(float x, float y, unsigned sg, unsigned (&p)[NP]) {
-  if constexpr (SIGN) {
-    x = flip(x, sg);
-    y = flip(y, sg);
+// Two values' parts, packed per plane.  Three parts: of the values times f.
+template <int NP>
+__device__ __forceinline__ void split_pair(float x, float y, float f, unsigned (&p)[NP]) {
+  if constexpr (NP == 3) {
+    x *= f;
+    y *= f;
   }
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
@@ -162,7 +167,7 @@ struct FLoadKC {
     u32x4 v[PER];
   };
   unsigned off[PER];  // bytes from (row r0, the stage's k); rows clamped to the last
-  unsigned sign[PER];  // sign bit of the chunk's row (signs())
+  float factor[PER];   // kUp with the sign of the chunk's row (signs())
   int r0, rows;
   long long ld, bytes;
   const S* src;
@@ -181,8 +186,8 @@ struct FLoadKC {
       off[i] = (unsigned)(((long long)r * ld + (c % CPR) * 4) * ES);
     }
   }
-  // The rows' signs, for the split and (table) the results.
-  __device__ __forceinline__ void signs(unsigned* table, int K, int tid) {
+  // The rows' signs, on the factors of the split and (table) the results.
+  __device__ __forceinline__ void signs(float* table, int K, int tid) {
     const long long base = ES * (long long)r0 * ld;
     const __amdgpu_buffer_rsrc_t rs = panel_rsrc(src, base, bytes);
 #pragma unroll
@@ -190,8 +195,9 @@ struct FLoadKC {
       const int c = tid + i * C::THREADS;
       const u32x4 v = load_chunk<MODE, S>(rs, src, (long long)min(r0 + c / CPR, rows - 1) * ld,
                                        off[i] - (unsigned)((c % CPR) * 4 * ES), K);
-      sign[i] = row_sign(v[0] ^ v[1] ^ v[2] ^ v[3]);
-      if (c % CPR == 0) table[c / CPR] = sign[i];
+      const unsigned bits = v[0] ^ v[1] ^ v[2] ^ v[3];
+      factor[i] = signed_by(kUp, bits);
+      if (c % CPR == 0) table[c / CPR] = signed_by(kDown, bits);
     }
   }
   __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
@@ -215,8 +221,8 @@ struct FLoadKC {
       unsigned p[2][C::NP];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        split_pair<SIGN>(elem<MODE, S>(g.v[i], 2 * h), elem<MODE, S>(g.v[i], 2 * h + 1),
-                         SIGN ? sign[i] : 0u, p[h]);
+        split_pair(elem<MODE, S>(g.v[i], 2 * h), elem<MODE, S>(g.v[i], 2 * h + 1),
+                   SIGN ? factor[i] : kUp, p[h]);
 #pragma unroll
       for (int q = 0; q < C::NP; ++q) {
         u32x2 w;
@@ -249,7 +255,7 @@ struct FLoadRC {
     u32x4 v[PER][KB];
   };
   unsigned off[PER];  // bytes from (row r0, the stage's k)
-  unsigned sign[PER];  // sign bit of the block's first row (signs())
+  float factor[PER];   // kUp with the sign of the block's first row (signs())
   int r0, rows;
   long long ld, bytes;
   const S* src;
@@ -267,10 +273,11 @@ struct FLoadRC {
       off[i] = (unsigned)(((long long)(c % NKB) * KB * ld + (c / NKB) * 4) * ES);
     }
   }
-  __device__ __forceinline__ void signs(unsigned* table, int, int tid) {
+  __device__ __forceinline__ void signs(float* table, int, int tid) {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) sign[i] = row_sign(r0 + (tid + i * C::THREADS) / NKB * 4);
-    if (tid < R) table[tid] = row_sign(r0 + tid);
+    for (int i = 0; i < PER; ++i)
+      factor[i] = signed_by(kUp, r0 + (tid + i * C::THREADS) / NKB * 4);
+    if (tid < R) table[tid] = signed_by(kDown, r0 + tid);
   }
   __device__ __forceinline__ void load(Regs& g, int k0, int kend, int tid) const {
     const long long base = ES * ((long long)k0 * ld + r0);
@@ -299,8 +306,8 @@ struct FLoadRC {
         unsigned p[KB / 2][C::NP];
 #pragma unroll
         for (int h = 0; h < KB / 2; ++h)  // (r0 and the block are multiples of 4)
-          split_pair<SIGN>(elem<MODE, S>(g.v[i][2 * h], e), elem<MODE, S>(g.v[i][2 * h + 1], e),
-                           SIGN ? sign[i] ^ row_sign(e) : 0u, p[h]);
+          split_pair(elem<MODE, S>(g.v[i][2 * h], e), elem<MODE, S>(g.v[i][2 * h + 1], e),
+                     SIGN ? signed_by(factor[i], e) : kUp, p[h]);
 #pragma unroll
         for (int q = 0; q < C::NP; ++q) {
           if constexpr (KB == 4) {
@@ -339,11 +346,11 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Workgroup w of a product's nwg.  smem: C::LDS bytes; row_signs: C::BM words
+// Workgroup w of a product's nwg.  smem: C::LDS bytes; row_factors: C::BM words
 // (fp32 products).
 template <class C, bool A_KC, bool B_KC, int MODE, class S>
 __device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
-                                            unsigned char* smem, unsigned* row_signs) {
+                                            unsigned char* smem, float* row_factors) {
   const TileIdx ti = tile_of(g, w, nwg);
   const int m0 = ti.tm * C::BM;
   const int n0 = ti.tn * C::BN;
@@ -430,7 +437,7 @@ __device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
 
 #pragma unroll
   for (int p = 0; p < C::D; ++p) load(p, p);
-  if constexpr (F32) la.signs(row_signs, g.K, tid);
+  if constexpr (F32) la.signs(row_factors, g.K, tid);
   store(0, 0);
   lds_only_barrier();
   for (int k0 = 0; k0 < nk; k0 += C::D) {
@@ -453,12 +460,9 @@ __device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const unsigned sg = row_signs[wm0 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
+        const float f = row_factors[wm0 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
 #pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-          const float x = acc[i][j][e];
-          acc[i][j][e] = flip(x, sg);
-        }
+        for (int j = 0; j < C::FN; ++j) acc[i][j][e] *= f;
       }
 
     // Results that are not finite: once more in fp32 (see the top of the file).
@@ -512,8 +516,8 @@ __device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
 template <class C, bool A_KC, bool B_KC, int MODE, class S>
 __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_kernel(KernelArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
-  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
-  staged_tile<C, A_KC, B_KC, MODE, S>(g, blockIdx.x, gridDim.x, smem, row_signs);
+  __shared__ float row_factors[C::NP == 3 ? C::BM : 1];
+  staged_tile<C, A_KC, B_KC, MODE, S>(g, blockIdx.x, gridDim.x, smem, row_factors);
 }
 
 // dX (n1 workgroups; W read as it lies, row-contiguous, so bf16 needs no
@@ -524,10 +528,10 @@ __global__ __launch_bounds__(C::THREADS, 2) void gemm_staged_pair_kernel(KernelA
                                                                          KernelArgs g2, int n2,
                                                                          bool dw_first) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS];
-  __shared__ unsigned row_signs[C::NP == 3 ? C::BM : 1];
+  __shared__ float row_factors[C::NP == 3 ? C::BM : 1];
   const PairIdx p = pair_index(n1, n2, dw_first);
-  if (p.dx) staged_tile<C, true, false, kChunk, S>(g1, p.w, n1, smem, row_signs);
-  else staged_tile<C, false, false, kChunk, S>(g2, p.w, n2, smem, row_signs);
+  if (p.dx) staged_tile<C, true, false, kChunk, S>(g1, p.w, n1, smem, row_factors);
+  else staged_tile<C, false, false, kChunk, S>(g2, p.w, n2, smem, row_factors);
 }
 
 // Tiles.  Big: 8 waves of 64 x 128, one workgroup per CU; fewest bytes and

@@ -1,5 +1,6 @@
 """fp32 products through the bf16 matrix units (three-part operands): every
-layout at the tiles' edges, each way of loading, values outside bf16's range.
+layout at the tiles' edges, each way of loading, values outside bf16's range
+and below it.
 
 Bound per element: the 6 ceil(K / 16) additions of a chain each round by at
 most 2^-24 of the running sum, which stays below S = sum_k |a b|; the terms
@@ -87,6 +88,40 @@ def test_values_beyond_bf16(op, value):
     np.testing.assert_array_equal(out[~fine & ~np.isnan(ref)], ref[~fine & ~np.isnan(ref)])
     bound = 2 * (K + 1) * 2.0 ** -24 * (a.abs() @ b.abs()).cpu().numpy()
     assert (np.abs(out[fine] - ref[fine]) <= bound[fine]).all()
+
+
+@pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN, sru.OP_TN])
+@pytest.mark.parametrize("scale", [2.0 ** -112, 2.0 ** -122, 2.0 ** -133])
+def test_small_values(op, scale):
+    """Operands whose parts would lie below bf16's range, down to fp32's own
+    subnormal ones: the bound of any other product, and the rounding of
+    results (and of partial sums) below 2^-126."""
+    M, N, K = 200, 140, 77
+    for tiny in (0, 1):
+        pair = list(operands(op, M, N, K))
+        pair[tiny] = pair[tiny] * scale
+        out = product(op, *pair, M, N, K)
+        a, b = canonical(op, *pair)
+        bound = (2 * (6 * -(-K // 16) + 1) * 2.0 ** -24 * (a.abs() @ b.abs()) + 64 * 2.0 ** -149)
+        err = (out.double() - a @ b).abs()
+        assert bool((err <= bound).all()), (tiny, float((err / bound).max()))
+
+
+def test_small_gradients():
+    """A backward pass is linear in dH: 2^-120 of it gives 2^-120 of every
+    gradient, to fp32 rounding (2^-149 is 2^-26 of the smaller dU)."""
+    L, B, d_in, d = 20, 9, 76, 100
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+    X, W, dH = rand(L, B, d_in), rand(1, 4, d, d_in) * d_in ** -0.5, rand(L, B, d)
+    p = [rand(1, d) * 0.3 for _ in range(4)]
+    fw = sru.forward(X, W, *p)
+    whole = sru.backward(X, W, *p, fw["U"], fw["C"], dH)
+    small = sru.backward(X, W, *p, fw["U"], fw["C"], dH * 2.0 ** -120)
+    torch.cuda.synchronize()
+    for n in ("dX", "dW"):
+        want, got = whole[n].double(), small[n].double() * 2.0 ** 120
+        assert float((got - want).norm() / want.norm()) < 1e-6, n
 
 
 @pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN, sru.OP_TN])
