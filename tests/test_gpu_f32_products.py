@@ -140,6 +140,23 @@ def test_no_common_sign_in_errors(op, K):
     assert float(z.abs().max()) < 5.0, z
 
 
+@pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN])
+@pytest.mark.parametrize("K", [32, 77, 128, 1000])
+@pytest.mark.parametrize("lead,count", [(0.0, 16), (1.0, 8)])
+def test_no_common_sign_with_equal_leading_values(op, K, lead, count):
+    """The same where every row begins with the same values (fewer than a
+    slab of 16 where they are not zero: the rounding of a whole slab of equal
+    values is the same in every row, whatever its sign)."""
+    M, N = 12800, 96
+    A, B = operands(op, M, N, K)
+    A[:, :count] = lead
+    out = product(op, A, B, M, N, K)
+    a, b = canonical(op, A, B)
+    err = out.double() - a @ b
+    z = err.mean(0) / (err.std(0) / M ** 0.5)
+    assert float(z.abs().max()) < 5.0, z
+
+
 def test_same_bits_at_every_row_and_size():
     """A row's results depend on its values alone, whichever tile runs it."""
     N, K = 768, 200
