@@ -57,9 +57,10 @@
 //
 // A value that is not finite after this (infinities, NaN, magnitudes above
 // 2^103 = 1e31) turns its second part, and so every result it enters, into
-// NaN, and results above 2^79 may overflow.  A workgroup that finds a result
-// that is not finite therefore runs its tile again with the fp32 matrix
-// instruction: such results are fp32 arithmetic's own.
+// NaN, and results above 2^79 may overflow.  A wave that finds a result that
+// is not finite therefore computes the 32 x 32 blocks that hold one again with
+// the fp32 matrix instruction, and writes these results alone: they are fp32
+// arithmetic's own, and the finite ones beside them keep their bits.
 #include <algorithm>
 
 #include "sru_gemm_tile.h"
@@ -81,13 +82,12 @@ struct FCfg {
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int FM = WM / 32, FN = WN / 32;
   static constexpr int THREADS = WAVES * 64;
-  // bytes of an LDS row: bf16 plane, fp32 tile (the rerun).  16 bytes of
-  // padding keep the 16 rows of a fragment read on distinct banks.
-  static constexpr int ROWB = 2 * BK + 16, ROWF = 4 * BK + 16;
+  // bytes of an LDS row.  16 bytes of padding keep the 16 rows of a fragment
+  // read on distinct banks.
+  static constexpr int ROWB = 2 * BK + 16;
   static constexpr int A_PLANE = BM * ROWB, B_PLANE = BN * ROWB;
   static constexpr int STAGE = NP * (A_PLANE + B_PLANE);
   static constexpr int LDS = 2 * STAGE;  // two buffers
-  static_assert(NP == 1 || (BM + BN) * ROWF <= LDS, "the rerun's fp32 tile fits");
   static_assert(LDS <= 160 * 1024 && BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile");
 };
 
@@ -248,13 +248,6 @@ struct FLoadKC {
       }
     }
   }
-  __device__ __forceinline__ void store_f32(const Regs& g, unsigned char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-      *reinterpret_cast<u32x4*>(lds + (c / CPR) * C::ROWF + (c % CPR) * 16) = g.v[i];
-    }
-  }
 };
 
 // Row-contiguous operand: element (r, k) at src[k*ld + r].  A thread owns KB
@@ -338,18 +331,6 @@ struct FLoadRC {
       }
     }
   }
-  __device__ __forceinline__ void store_f32(const Regs& g, unsigned char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int c = tid + i * C::THREADS;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk)
-          *reinterpret_cast<float*>(lds + ((c / NKB) * 4 + e) * C::ROWF +
-                                    ((c % NKB) * KB + kk) * 4) = elem<MODE, S>(g.v[i][kk], e);
-    }
-  }
 };
 
 // Workgroup barrier that waits for this wave's LDS accesses only: the fence
@@ -360,6 +341,54 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// The 32 x 32 block of results at (m0, n0), already written, over k in [kbeg,
+// kend) on the fp32 instruction, put where the results are not finite.  One
+// wave; operands straight from memory, 16 k in flight.
+template <bool A_KC, bool B_KC>
+__device__ __forceinline__ void fp32_block(const KernelArgs& g, int m0, int n0, int kbeg, int kend,
+                                           int lane, int split) {
+  float* out = g.out + (long long)split * g.split_stride;
+  const int n = n0 + (lane & 31), mb = m0 + (lane >> 5) * 4;
+  bool bad = false;
+  for (int e = 0; e < 16; ++e) {
+    const int m = mb + (e >> 2) * 8 + (e & 3);
+    if (m < g.M && n < g.N) bad |= !(out[(long long)m * g.ldo + n] * 0.f == 0.f);
+  }
+  if (__ballot(bad) == 0) return;
+  // rows and columns past the end repeat the last: their results are not used
+  const long long ar = min(m0 + (lane & 31), g.M - 1), br = min(n, g.N - 1);
+  const float* ap = static_cast<const float*>(g.A) + (A_KC ? ar * g.lda : ar);
+  const float* bp = static_cast<const float*>(g.B) + (B_KC ? br * g.ldb : br);
+  floatx16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int k0 = kbeg; k0 < kend; k0 += 16) {
+    float af[8], bf[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const int k = k0 + 2 * s + (lane >> 5), kc = min(k, kend - 1);
+      const float x = ap[A_KC ? kc : kc * g.lda], y = bp[B_KC ? kc : kc * g.ldb];
+      af[s] = k < kend ? x : 0.f;
+      bf[s] = k < kend ? y : 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[s], bf[s], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int m = mb + (e >> 2) * 8 + (e & 3);
+    if (m < g.M && n < g.N) {
+      float* o = out + (long long)m * g.ldo + n;
+      const float* add = g.add + (long long)m * g.add_ld + n;
+      float v = acc[e];
+      if (g.add_count > 0) v += add[0];
+      if (g.add_count > 1) v += add[g.add_off];
+      if (!(*o * 0.f == 0.f)) *o = v;
+    }
+  }
 }
 
 // Workgroup w of a product's nwg.  smem: C::LDS bytes; row_factors: C::BM words
@@ -480,53 +509,27 @@ __device__ __forceinline__ void staged_tile(const KernelArgs& g, int w, int nwg,
 #pragma unroll
         for (int j = 0; j < C::FN; ++j) acc[i][j][e] *= f;
       }
-
-    // Results that are not finite: once more in fp32 (see the top of the file).
-    float z = 0.f;
+  }
+  float z = 0.f;  // NaN where a result is not finite
+  if constexpr (F32) {
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
       for (int j = 0; j < C::FN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) z = fmaf(acc[i][j][e], 0.f, z);
-    unsigned* flag = reinterpret_cast<unsigned*>(smem);
-    const bool bad = __ballot(!(z == 0.f)) != 0;
-    if (lane == 0) flag[wave] = bad;
-    lds_only_barrier();
-    unsigned any = 0;
-#pragma unroll
-    for (int i = 0; i < C::WAVES; ++i) any |= flag[i];
-    if (__builtin_amdgcn_readfirstlane(any)) {
-      clear();
-      for (int kt = 0; kt < nk; ++kt) {
-        load(0, kt);
-        lds_only_barrier();  // every wave is done with the tile (the flags)
-        la.store_f32(ra[0], smem, tid);
-        lb.store_f32(rb[0], smem + C::BM * C::ROWF, tid);
-        lds_only_barrier();
-        for (int ks = 0; ks < C::BK; ks += 2) {
-          const int ko = (ks + (lane >> 5)) * 4;
-          float af[C::FM], bf[C::FN];
-#pragma unroll
-          for (int i = 0; i < C::FM; ++i)
-            af[i] = *reinterpret_cast<const float*>(smem + (wm0 + i * 32 + (lane & 31)) * C::ROWF +
-                                                    ko);
-#pragma unroll
-          for (int j = 0; j < C::FN; ++j)
-            bf[j] = *reinterpret_cast<const float*>(
-                smem + (C::BM + wn0 + j * 32 + (lane & 31)) * C::ROWF + ko);
-#pragma unroll
-          for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-            for (int j = 0; j < C::FN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-        }
-      }
-    }
   }
   if (g.add_count == 0) write_tile_add<C, 0>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
   else if (g.add_count == 1) write_tile_add<C, 1>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
   else write_tile_add<C, 2>(g, acc, m0, n0, wm0, wn0, lane, ti.split);
+  if constexpr (F32) {
+    if (__ballot(!(z == 0.f)) != 0) {
+      for (int i = 0; i < C::FM; ++i)
+        for (int j = 0; j < C::FN; ++j)
+          fp32_block<A_KC, B_KC>(g, m0 + wm0 + i * 32, n0 + wn0 + j * 32, kbeg, kend, lane,
+                                 ti.split);
+    }
+  }
 }
 
 template <class C, bool A_KC, bool B_KC, int MODE, class S>

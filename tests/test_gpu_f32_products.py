@@ -91,6 +91,23 @@ def test_values_beyond_bf16(op, value):
 
 
 @pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN, sru.OP_TN])
+@pytest.mark.parametrize("shape", [(200, 140, 50), (1030, 1028, 260), (4100, 2052, 132)])
+def test_finite_results_beside_others_keep_their_bits(op, shape):
+    """A row of A and a column of B with values that are not finite change no
+    other row and column (one shape for each tile)."""
+    M, N, K = shape
+    A, B = operands(op, M, N, K)
+    ref = product(op, A, B, M, N, K)
+    m, n = M // 2 + 3, N // 2 + 5
+    (A.t() if op == sru.OP_TN else A)[m, K // 2] = float("inf")
+    (B if op == sru.OP_NT else B.t())[n, 7] = float("nan")
+    out = product(op, A, B, M, N, K)
+    assert not torch.isfinite(out[m]).any() and not torch.isfinite(out[:, n]).any()
+    out[m], out[:, n] = ref[m], ref[:, n]
+    assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN, sru.OP_TN])
 @pytest.mark.parametrize("scale", [2.0 ** -112, 2.0 ** -122, 2.0 ** -133])
 def test_small_values(op, scale):
     """Operands whose parts would lie below bf16's range, down to fp32's own
