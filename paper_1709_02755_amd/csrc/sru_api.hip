@@ -515,7 +515,7 @@ int sru_forward(const float* X, const float* W, const float* v_f, const float* v
   // weights rounded), so both operands of the product are K-contiguous bf16.
   const void* Wop = W;
   const void* Xop = X;
-  const bool step = fused && s.M <= sru::kStepMaxTokens && L <= sru::kStepMaxLen;
+  const bool step = fused && sru::step_few_tokens(s.M, L, s.nfeat);
   if (bf16) {
     uint16_t* wb = W_bf16 ? W_bf16 : static_cast<uint16_t*>(workspace);
     if (!w_rounded) {
@@ -526,7 +526,7 @@ int sru_forward(const float* X, const float* W, const float* v_f, const float* v
     Wop = wb;
     if (X_bf16) {
       Xop = X_bf16;
-    } else if (step && aligned16(X)) {
+    } else if (step && sru::step_rounds_x(s.M, d_in, s.nfeat) && aligned16(X)) {
       Xop = nullptr;  // the kernel rounds X itself (16-byte loads)
     } else {
       uint16_t* xb = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) +

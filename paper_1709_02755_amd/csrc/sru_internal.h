@@ -162,11 +162,27 @@ struct FusedFwdArgs {
   int reset_new, linear;
 };
 hipError_t proj_scan_forward_launch(const FusedFwdArgs& a, hipStream_t stream);
-// The same for few tokens (sru_step.hip): at most kStepMaxTokens, and few
-// enough steps that the serial scan stays short.  Xb may be null: X is then
-// rounded by the kernel.
-constexpr long long kStepMaxTokens = 128;
+// The same for few tokens (sru_step.hip).  Every workgroup, one for 8 of the
+// nfeat = ndir d units, reads all of X, so the tiled kernel catches up with
+// the tokens and the units.  Measured against it, both with X in fp32, over
+// d_in 256 to 4096, nfeat 256 to 4096 and up to 8 steps: ahead up to 96 tokens
+// (8 steps of 8, d 4096 71 -> 53 us; 4 x 24, d 2048 in both directions, 38.8
+// against 39.5 us from bf16 X, is the closest), and up to 128 at 2048 units
+// (2 x 64, d 2048 41.0 -> 39.8; 1 x 128, d 768 21.9 against 23.9 us the one
+// shape behind).  Past that only for one or two steps, of which a tile holds
+// few tokens (2 x 64, d 4096 150 -> 88 us, but 4 x 32 76 against 86 us).
 constexpr int kStepMaxLen = 8;
+inline bool step_few_tokens(long long tokens, int L, long long nfeat) {
+  return L <= kStepMaxLen && tokens <= (nfeat <= 2048 || L <= 2 ? 128 : 96);
+}
+// Xb may then be null: X is rounded by the kernel, which saves a launch of 2
+// us but has every workgroup read twice the bytes.  From fp32 X against rounded
+// first: 65 tokens of 512 -> 2048 units 14.6 against 15.5 us, 128 of 256 ->
+// 256 13.3 against 17.1; 128 of 1024 -> 1024 26.6 against 22; 64 of 4096 ->
+// 4096 75 against 53.
+inline bool step_rounds_x(long long tokens, long long d_in, long long nfeat) {
+  return tokens * d_in <= 48 * 1024 && tokens * d_in * nfeat <= (48LL * 1024) * 2048;
+}
 hipError_t step_forward_launch(const FusedFwdArgs& a, hipStream_t stream);
 
 // ----------------------------------------------------------------- scans

@@ -7,10 +7,10 @@
 // is one wave and owns 8 hidden units of one direction: their k gate rows of
 // Wcat are the 32 columns of one 32-column MFMA block (k = 3: 24 and zeros),
 // the tokens its rows (FM blocks of 32).  d = 1024 then takes 128 CUs, and
-// each reads 64 KiB.  Both operands go straight from memory into registers in
+// each reads 48 KiB (k = 3; 64 for k = 4).  Both operands go straight from memory into registers in
 // the MFMA's layout, 16 bytes a lane, two sets of S slabs (16 k) in flight;
-// X is rounded on the way (RNE) unless the caller holds it in bf16, which
-// saves the launch that would round it.  The slabs accumulate in the order of
+// X is rounded on the way (RNE) where that beats a launch that rounds it first
+// (step_rounds_x), unless the caller holds it in bf16.  The slabs accumulate in the order of
 // the other products, so U has their bits; it passes through LDS, where the
 // scan gives each lane one (sequence, unit).
 //
@@ -162,8 +162,9 @@ void launch_step_rows(const FusedFwdArgs& a, hipStream_t st) {
 }  // namespace
 
 hipError_t step_forward_launch(const FusedFwdArgs& a, hipStream_t st) {
-  if ((a.k != 3 && a.k != 4) || (long long)a.L * a.B > kStepMaxTokens || a.d % kStepUnits != 0 ||
-      !a.X || (a.k == 3 && a.d_in != a.d))
+  const long long tokens = (long long)a.L * a.B, nfeat = (long long)a.ndir * a.d;
+  if ((a.k != 3 && a.k != 4) || !step_few_tokens(tokens, a.L, nfeat) || a.d % kStepUnits != 0 ||
+      !a.X || (a.k == 3 && a.d_in != a.d) || (!a.Xb && !step_rounds_x(tokens, a.d_in, nfeat)))
     return hipErrorInvalidValue;
   timing_before("proj_scan_fwd", st);
   if (a.k == 3) launch_step_rows<3>(a, st);

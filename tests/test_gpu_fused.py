@@ -5,6 +5,8 @@ k = 3 and 4, tile plans of 2, 4 and 8 sequences, several time blocks per
 tile, ragged step and sequence counts, every direction, padding, c0 and the
 gate variants; and against the oracle, the linear recurrence included."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -162,7 +164,35 @@ FEW = [
     (2, 64, 256, 256, O.DIR_REV, False, 1.0, False),
     (1, 128, 1000, 64, O.DIR_FWD, True, 1.0, False),
     (7, 18, 72, 128, O.DIR_BI, True, 1.0, False),
+    # both sides of the lines: X rounded by the kernel or first, this kernel or
+    # the tiled one (128 tokens; 96 past 2048 units and two steps)
+    (4, 20, 600, 128, O.DIR_FWD, True, 1.0, False),
+    (5, 17, 600, 128, O.DIR_FWD, False, 1.0, False),
+    (2, 64, 72, 2112, O.DIR_FWD, False, 1.0, False),
+    (3, 32, 64, 1088, O.DIR_BI, False, 1.0, False),
+    (3, 33, 64, 2112, O.DIR_REV, False, 1.0, False),
+    (3, 43, 72, 64, O.DIR_FWD, True, 1.0, False),
 ]
+
+
+@pytest.mark.parametrize("L,B,d_in,d,rounds", [(1, 64, 768, 128, False), (1, 64, 776, 128, True),
+                                               (2, 64, 1024, 1024, True), (1, 24, 1024, 4096, False),
+                                               (5, 5, 1024, 4096, True)])
+def test_few_tokens_round_x_first_where_that_is_faster(L, B, d_in, d, rounds):
+    """The kernels of a call with fp32 X."""
+    X = torch.randn((L, B, d_in), device="cuda")
+    W = torch.randn((1, 3 if d == d_in else 4, d, d_in), device="cuda")
+    p = [torch.zeros((1, d), device="cuda") for _ in range(4)]
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+    for e in events:
+        e.record()
+    handles = (ctypes.c_void_p * 8)(*[e.cuda_event for e in events])
+    lib = sru.lib()
+    assert lib.sru_timing_begin(handles, 8) == 0
+    sru.forward(X, W.bfloat16(), *p, gemm_dtype=O.GEMM_BF16, store_c=False, keep_u=False)
+    labels = [lib.sru_timing_label(i).decode() for i in range(lib.sru_timing_end())]
+    torch.cuda.synchronize()
+    assert labels == (["bf16_x"] if rounds else []) + ["proj_scan_fwd"]
 
 
 @pytest.mark.parametrize("case", FEW)
