@@ -31,9 +31,9 @@
 // four values alone, and those zero in every row, the mean error over 12,800
 // rows of 1000 values was 15 standard errors from zero; eight groups instead
 // of four cost 2 % more of a product).  The row's values
-// alone decide: its results are the same bits wherever it stands, however a
-// sequence is cut into calls.  For a row-contiguous A (a sum over tokens) the
-// row's index decides.
+// alone decide: its results, where K is not split, are the same bits wherever
+// it stands, however a sequence is cut into calls.  For a row-contiguous A (a
+// sum over tokens) the row's index decides.
 //
 // The parts are formed once per tile, between the global loads and LDS: the
 // tile's three planes lie in LDS as bf16 [rows][BK + 8], so a fragment of a
@@ -622,8 +622,8 @@ struct Plan {
 // fits whatever the pointers and pitches are.
 //
 // A K-contiguous product is split only where its 128 x 128 tiles fill at most
-// a quarter of the CUs: its other results do not depend on M, so that a
-// sequence cut into calls gives one call's bits.
+// a quarter of the CUs, and only dX asks for it: U does not depend on M, so
+// that a sequence cut into calls gives one call's bits.
 struct SplitRange {
   int lo, hi;
 };

@@ -130,7 +130,8 @@ def test_chunked_backward_carry_on_gpu(direction, gemm):
     """Truncation-free back-propagation in chunks: forward over the chunks
     with c_last -> c0, backward over them in reverse processing order with
     dc0 -> dc_last.  H, dX and dc0 equal the one-call layer bit for bit (the
-    same operations per step and per output row); parameter gradients are
+    same operations per step and, as dX is cut into as many parts in every
+    call at these sizes, per output row); parameter gradients are
     the chunks' sum, equal to the one-call ones within the tolerance (a
     different summation order)."""
     L, B, d, h = 40, 6, 128, 24
@@ -163,6 +164,43 @@ def test_chunked_backward_carry_on_gpu(direction, gemm):
     tol = TOL_FP32 if gemm == O.GEMM_FP32 else 1e-5
     for k in ("dW", "dv_f", "dv_r", "db_f", "db_r"):
         check(k, ga[k] + gs[k], host(fb[k]), tol)
+
+
+@pytest.mark.parametrize("gemm,L,B,d,h", [
+    (O.GEMM_FP32, 160, 32, 200, 130),   # one call's dX unsplit, the 30 steps' split
+    (O.GEMM_FP32, 64, 24, 256, 54),     # different numbers of parts
+    (O.GEMM_BF16, 160, 16, 416, 150),
+    (O.GEMM_BF16, 70, 7, 1000, 60)])
+def test_chunked_backward_carry_split_dx(gemm, L, B, d, h):
+    """Chunked back-propagation at sizes whose dX is summed in another number
+    of parts in each call: U, H, C, c_last and dc0 keep one call's bits, dX
+    differs by the order of its sum alone.  (In bf16 mode dU's rounding is the
+    same in all calls.)"""
+    print(f"chunked backward, split dX, gemm={gemm} L={L} B={B} d={d}", flush=True)
+    c = random_layer_case(np.random.default_rng(41), L, B, d, d, O.DIR_FWD, c0=True, dc_last=True,
+                          bias_scale=0.5)
+    X, W = dev(c["X"]), dev(c["W"])
+    p = [dev(c[k]) for k in ("v_f", "v_r", "b_f", "b_r")]
+    c0, dcl, dH = dev(c["c0"]), dev(c["dc_last"]), dev(c["dH"])
+
+    def call(s, c0, dc_last):
+        x = X[s].contiguous()
+        f = sru.forward(x, W, *p, c0=c0, gemm_dtype=gemm)
+        return f, lambda dc: sru.backward(x, W, *p, f["U"], f["C"], dH[s].contiguous(), c0=c0,
+                                          dc_last=dc, gemm_dtype=gemm)
+
+    full, back = call(slice(0, L), c0, dcl)
+    fb = back(dcl)
+    fa, back_a = call(slice(0, h), c0, None)
+    fs, back_s = call(slice(h, L), fa["c_last"], None)
+    gs = back_s(dcl)
+    ga = back_a(gs["dc0"])
+    torch.cuda.synchronize()
+    for k in ("U", "H", "C"):
+        assert torch.equal(torch.cat([fa[k], fs[k]]), full[k]), k
+    assert torch.equal(fs["c_last"], full["c_last"])
+    assert torch.equal(ga["dc0"], fb["dc0"])
+    check("dX", torch.cat([ga["dX"], gs["dX"]]), host(fb["dX"]), TOL_FP32)
 
 
 @pytest.mark.parametrize("direction", [O.DIR_FWD, O.DIR_REV])
