@@ -1367,7 +1367,9 @@ GemmPairPlan gemm_pair_plan(const GemmDesc& gx, const GemmDesc& gx_nn, const Gem
 hipError_t gemm_pair_launch(const GemmDesc& gx, const GemmDesc& gw, hipStream_t st) {
   const bool dx = direct_ok(gx) && direct_ok(gw);
   if (!dx && (gx.b_kc || !gemm_staged_pair_launch(gx, gw, st))) {
-    // operands that need other loads than the plan assumed
+    // operands that need other loads than the plan assumed: fp32 ones of a
+    // caller, on 4 bytes (bf16 ones are in the workspace or on 16 bytes)
+    if (gx.bf16) return hipErrorInvalidValue;
     if (hipError_t e = gemm_launch(gx, st)) return e;
     return gemm_launch(gw, st);
   }

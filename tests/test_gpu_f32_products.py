@@ -7,6 +7,8 @@ most 2^-24 of the running sum, which stays below S = sum_k |a b|; the terms
 left out and the rounding inside a matrix instruction are covered by the
 factor 2.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -68,6 +70,47 @@ def test_unaligned_operands_same_bits(op):
 
     out = product(op, shifted(A), shifted(B), M, N, K)
     assert torch.equal(out, ref)
+
+
+def labelled(call):
+    """The call's result and the names of its kernels."""
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(16)]
+    for e in events:
+        e.record()
+    handles = (ctypes.c_void_p * 16)(*[e.cuda_event for e in events])
+    lib = sru.lib()
+    assert lib.sru_timing_begin(handles, 16) == 0
+    out = call()
+    labels = [lib.sru_timing_label(i).decode() for i in range(lib.sru_timing_end())]
+    torch.cuda.synchronize()
+    return out, labels
+
+
+@pytest.mark.parametrize("L,B,d_in,d", [(64, 32, 256, 256), (20, 4, 64, 64), (33, 9, 100, 76)])
+@pytest.mark.parametrize("shift_x,shift_w", [(True, False), (False, True), (True, True)])
+def test_backward_pair_of_unaligned_operands(L, B, d_in, d, shift_x, shift_w):
+    """Sizes whose dX and dW run in one launch: X or W on 4 bytes makes two
+    launches of it, and the same bits (the same tiles and parts)."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, device="cuda")
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+
+    X, W = rand(L, B, d_in), rand(1, 3 if d == d_in else 4, d, d_in) * d_in ** -0.5
+    dH = rand(L, B, d)
+    p = [rand(1, d) * 0.3 for _ in range(4)]
+    fw = sru.forward(X, W, *p)
+    ref, labels = labelled(lambda: sru.backward(X, W, *p, fw["U"], fw["C"], dH))
+    assert "gemm_dx_dw" in labels, labels
+    out, labels = labelled(lambda: sru.backward(shifted(X) if shift_x else X,
+                                                shifted(W) if shift_w else W, *p, fw["U"],
+                                                fw["C"], dH))
+    assert "gemm_dx" in labels and "gemm_dw" in labels and "gemm_dx_dw" not in labels, labels
+    for n in ("dX", "dW", "dv_f", "dv_r", "db_f", "db_r"):
+        assert torch.equal(out[n], ref[n]), n
 
 
 @pytest.mark.parametrize("op", [sru.OP_NT, sru.OP_NN, sru.OP_TN])
