@@ -210,10 +210,10 @@ SRU_API int sru_forward_noalloc(const float* X, const float* W,
  *        [ndir, d], dc0 [B, ndir*d] (NULL = do not compute).
  *   bf16 companions (SRU_GEMM_BF16 only, else NULL; each may be NULL; as
  *   in sru_forward): X_bf16 = X rounded to bf16; W_bf16 = Wcat rounded to
- *   bf16 (the W_bf16 sru_forward wrote; the dX product reads its transposed
- *   copy, made in the workspace).  NULL: rounded into the workspace.  W
- *   may be NULL when W_bf16 is given (weights held in bf16, as in
- *   sru_forward); dW is still written in fp32.
+ *   bf16 (the W_bf16 sru_forward wrote; the dX product reads it as it lies,
+ *   or a transposed copy made in the workspace, by the sizes).  NULL: rounded
+ *   into the workspace.  W may be NULL when W_bf16 is given (weights held in
+ *   bf16, as in sru_forward); dW is still written in fp32.
  * With the gated recurrence, a sequence cut into consecutive calls
  * (c_last -> c0 forward, dc0 -> dc_last backward) gives one call's U, H, C,
  * c_last and dc0 bit for bit, except dc0 with 8,192 to 32,767 lanes

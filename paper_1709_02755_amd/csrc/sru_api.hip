@@ -662,7 +662,8 @@ int sru_backward(const float* X, const float* W, const float* v_f, const float* 
   //    operands row-contiguous; dX reads Wcat^T rounded to bf16 into the
   //    workspace (a transposed copy of W_bf16 when the caller holds it, else
   //    rounded from W), both operands K-contiguous, so it runs at the speed
-  //    of the projection.  Split partials: see BwdLayout (with both
+  //    of the projection, or (nn: the staged pair) Wcat rounded, as it lies.
+  //    Split partials: see BwdLayout (with both
   //    products split and dX first, one launch sums both).
   auto round_x = [&]() -> int {
     if (!bf16 || X_bf16) return SRU_OK;
