@@ -239,8 +239,9 @@ __device__ __forceinline__ void write_tile_staged(const KernelArgs& g,
 // ---------------------------------------------------------------------------
 // bf16 x bf16 products with global -> LDS loads that bypass registers.
 // Buffer loads with the LDS flag write each lane's 16 bytes straight into
-// LDS at (wave-uniform base + 16 * lane); a ring of STAGES tiles lets the
-// loads run STAGES-1 K steps ahead of the MFMAs at no register cost.  Both
+// LDS at (wave-uniform base + 16 * lane); a ring of two tiles lets the loads
+// run a K step ahead of the MFMAs (A, in a third slot, two) at no register
+// cost.  Both
 // operands have the same layout, selected by RC:
 //
 // K-contiguous (RC = false; U = X W^T and dX = dU W as dU (W^T)^T):
@@ -263,12 +264,11 @@ __device__ __forceinline__ void write_tile_staged(const KernelArgs& g,
 //   slots mod 16, i.e. all 64 banks once.  (An XOR by 2*(s & 3) put both
 //   groups on the same 8 slots: a two-way conflict on every read.)
 //
-// Each wave owns a 128 x 64 block of the tile (4 x 2 MFMA tiles of 32 x 32,
-// 128 accumulator registers per lane); two waves share each SIMD, so one's
-// LDS reads and barrier waits hide behind the other's MFMAs.  A 256 x 256
-// tile (8 waves) loads a third fewer bytes per flop than 256 x 128 (4
-// waves, two workgroups per CU); the loads, not the MFMAs, bound the
-// smaller tile.
+// Each wave of a big tile owns a 128 x 64 block of it (4 x 2 MFMA tiles of 32
+// x 32, 128 accumulator registers per lane); two waves share each SIMD, so
+// one's LDS reads and barrier waits hide behind the other's MFMAs.  A 256 x
+// 256 tile loads half the bytes per flop of a 128 x 128 one, which its loads
+// bound, not the MFMAs.
 template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int STAGES_, int SA_ = STAGES_>
 struct DCfg {
   // STAGES: slots of the B operand's ring; SA: slots of the A operand's
@@ -286,7 +286,7 @@ struct DCfg {
   static constexpr int LDS = SA * A_OPB + STAGES * B_OPB;  // A slots, then B slots
   static constexpr int OCC = LDS <= 80 * 1024 ? 2 : 1;  // workgroups per CU
   static_assert(SA == STAGES || SA == STAGES + 1, "A ring depth");
-  static_assert(BK == 32 || BK == 64, "k per stage");
+  static_assert(STAGES == 2 && BK == 64, "ring and k per stage");
   static_assert((WM == 128 && WN == 64) || (WM == 64 && (WN == 64 || WN == 96 || WN == 128)),
                 "wave block");
   static_assert(A_BPW * 1024 * WAVES == A_OPB && B_BPW * 1024 * WAVES == B_OPB,
@@ -326,8 +326,7 @@ struct DirectOperand {
   int kk[BPW];
 
   __device__ __forceinline__ static int swz(int r) {
-    if constexpr (BK == 32) return ((r >> 1) ^ (r >> 3)) & 3;
-    else return (r >> 1) & 7;
+    return (r >> 1) & 7;
   }
   __device__ __forceinline__ void init(int wave, int lane, int r0, int rows, long long ld) {
 #pragma unroll
@@ -448,31 +447,12 @@ __device__ __forceinline__ void direct_mainloop(unsigned char* smem, const OpA& 
   if constexpr (ALEAD)
     if (STAGES - 1 < nk) issue_a(STAGES - 1);
 
-  // Wait until this wave's part of stage kt has landed: the loads of later
-  // stages (IPS instructions per stage per wave) may stay in flight.  With
-  // the deeper A ring the loads go out in the order A(kt+1) ... B(kt) A(kt+1)
-  // B(kt+1) A(kt+2), so only A of step kt + 1 may remain (STAGES == 2).
+  // Wait until this wave's part of stage kt has landed.  With the deeper A
+  // ring the loads go out in the order A(kt+1) ... B(kt) A(kt+1) B(kt+1)
+  // A(kt+2), so A of step kt + 1 may stay in flight.
   auto wait_stage = [&](int kt) {
-    if constexpr (ALEAD) {
-      static_assert(STAGES == 2, "A lead with a 2-slot B ring");
-      if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(vm_wait(C::A_BPW));
-      else __builtin_amdgcn_s_waitcnt(vm_wait(0));
-      return;
-    }
-    const int later = min(STAGES - 2, nk - 1 - kt);
-    if constexpr (STAGES >= 4) {
-      if (later >= 2) {
-        __builtin_amdgcn_s_waitcnt(vm_wait(2 * C::IPS));
-        return;
-      }
-    }
-    if constexpr (STAGES >= 3) {
-      if (later >= 1) {
-        __builtin_amdgcn_s_waitcnt(vm_wait(C::IPS));
-        return;
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(vm_wait(0));
+    if (ALEAD && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(vm_wait(C::A_BPW));
+    else __builtin_amdgcn_s_waitcnt(vm_wait(0));
   };
   // Workgroup barrier without the release fence of __syncthreads (which
   // would wait for every outstanding vector memory operation, i.e. drain the
@@ -1010,17 +990,17 @@ __global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ 
   }
 }
 
-// Transposed: dst[c*rows + r] = bf16(src[r*cols + c]) through a 64x64 LDS tile.
-// Few workgroups at the sizes it meets, so bound by latency: a thread's 16
-// loads are all in flight before the first is used (8.6 us one by one at 1600 x
-// 300; the backward of L 77, B 13, 304 -> 200 in both directions 42.1 -> 38.3
-// us).  Rows and columns past the edge load the last one's.
 // Source element as fp32: fp32 as is, bf16 (raw bits) widened exactly.
 __device__ __forceinline__ float src_f32(float v) { return v; }
 __device__ __forceinline__ float src_f32(uint16_t v) {
   return __builtin_bit_cast(float, (unsigned)v << 16);
 }
 
+// Transposed: dst[c*rows + r] = bf16(src[r*cols + c]) through a 64x64 LDS tile.
+// Few workgroups at the sizes it meets, so bound by latency: a thread's 16
+// loads are all in flight before the first is used (8.6 us one by one at 1600 x
+// 300; the backward of L 77, B 13, 304 -> 200 in both directions 42.1 -> 38.3
+// us).  Rows and columns past the edge load the last one's.
 template <class S>
 __global__ __launch_bounds__(256) void to_bf16_t_kernel(const S* __restrict__ src, int rows,
                                                         int cols, uint16_t* __restrict__ dst) {
