@@ -49,9 +49,9 @@ def test_gemm_matches_matmul(op, dtype, shape):
     check("C", C, ref, TOL_FP32)
 
 
-def test_gemm_n96_tiles_at_the_shard_shape():
+def test_gemm_mid_tiles_at_the_shard_shape():
     """U = X W^T of one GPU's share of the 6-layer d = 1024 batch (2,048
-    tokens): 256 tiles of 256 x 96, every workgroup a full tile."""
+    tokens): 384 tiles of 128 x 128, every workgroup a full tile."""
     M, N, K = 2048, 3072, 1024
     print(f"gemm NT bf16 M={M} N={N} K={K}", flush=True)
     rng = np.random.default_rng(96)
