@@ -588,6 +588,14 @@ using FMid = FCfg<NP, 128, 128, NP == 3 ? 16 : 32, 2, 2, 2>;
 template <int NP>
 using FSmall = FCfg<NP, 64, 64, NP == 3 ? 32 : 64, 2, 2, 2>;
 
+// The tile for loads of single elements.  They take a register each, also in
+// bf16: with two stages in flight the big bf16 tile spilled 138 to 240 of them
+// to memory, so there one stage is in flight.  8733 x 7792 x 209 368 -> 182
+// us, 16384 x 903 x 301 116 -> 48, 7792 x 209 over 8733 tokens 205 -> 141.
+template <class C>
+using SingleCfg = FCfg<C::NP, C::BM, C::BN, C::BK, C::WAVES_M, C::WAVES_N,
+                       C::NP == 1 && C::BM == 256 ? 1 : C::D>;
+
 // Time of a product in us: per 16 k, one time for a workgroup alone on its CU
 // and one for each of several, and what a workgroup's start and end add; a
 // split adds its partials' traffic and the launch that sums them.  From times
@@ -710,7 +718,8 @@ hipError_t launch_staged(const GemmDesc& g, const KernelArgs& a, hipStream_t st)
   if (mode == kChunk)
     hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kChunk, S>), grid, block, 0, st, a);
   else if (mode == kSingle)
-    hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kSingle, S>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((gemm_staged_kernel<SingleCfg<C>, A_KC, B_KC, kSingle, S>), grid, block, 0,
+                       st, a);
   else
     hipLaunchKernelGGL((gemm_staged_kernel<C, A_KC, B_KC, kPlain, S>), grid, block, 0, st, a);
   return hipGetLastError();

@@ -29,6 +29,8 @@ CASES = [
     (33, 9, 100, 100, sru.DIR_REV),       # one addend, N no whole 16-byte chunks
     (61, 19, 84, 84, sru.DIR_BI),         # two addends
     (25, 4, 77, 52, sru.DIR_FWD),         # rows in single elements: not paired
+    (256, 64, 301, 301, sru.DIR_FWD),     # the same on big tiles
+    (128, 63, 67, 1001, sru.DIR_FWD),
 ]
 
 
