@@ -616,7 +616,33 @@ constexpr TileCost kTilesF32[3] = {{256, 256, FBig<3>::BK, 7.0, 2.35, 7.0, 2.4},
 constexpr TileCost kTilesBf16[3] = {{256, 256, FBig<1>::BK, 7.0, 0.80, 7.0, 0.80},
                                     {128, 128, FMid<1>::BK, 4.0, 0.30, 2.0, 0.25},
                                     {64, 64, FSmall<1>::BK, 3.0, 0.15, 1.5, 0.10}};
+// Loads of single elements, on every tile the bound of a step: by precision and
+// layout of A.  Of 58 sizes each (rows of 16 to 1,500 odd elements, up to
+// 30,000 tokens) every tile's times lie within 4 to 7 % of these (Small at few
+// steps 20 %).  With the chunk loads' times above the plan put sums over tokens
+// on Small tiles, whose element loads cost most: 3612 x 301 over 2048 tokens in
+// bf16 166 us, now 49 and 10 more for the split sum; 9264 x 186 over 2884 245
+// and 11, now 70 and 25; 7064 x 405 over 670 in fp32 113, now 48 and 20 more.
+constexpr TileCost kTilesSingle[2][2][3] = {
+    {{{256, 256, FBig<3>::BK, 9.5, 2.4, 6.0, 2.45},   // fp32, row-contiguous A
+      {128, 128, FMid<3>::BK, 6.5, 1.05, 2.5, 0.83},
+      {64, 64, FSmall<3>::BK, 2.3, 0.76, 1.5, 0.63}},
+     {{256, 256, FBig<3>::BK, 12.5, 2.8, 9.7, 3.1},   // K-contiguous
+      {128, 128, FMid<3>::BK, 7.5, 1.5, 3.0, 1.24},
+      {64, 64, FSmall<3>::BK, 4.8, 0.54, 2.5, 0.41}}},
+    {{{256, 256, FBig<1>::BK, 7.8, 1.58, 4.5, 1.58},  // bf16
+      {128, 128, FMid<1>::BK, 4.8, 0.70, 1.0, 0.65},
+      {64, 64, FSmall<1>::BK, 2.0, 0.65, 1.5, 0.61}},
+     {{256, 256, FBig<1>::BK, 11.2, 1.41, 9.7, 1.57},
+      {128, 128, FMid<1>::BK, 7.7, 0.70, 3.0, 0.66},
+      {64, 64, FSmall<1>::BK, 3.5, 0.28, 1.9, 0.23}}}};
 const TileCost& tile_cost(const GemmDesc& g, int t) { return (g.bf16 ? kTilesBf16 : kTilesF32)[t]; }
+// ... with the loads that the extents ask for (pitches and alignments are not
+// known when a workspace is sized)
+const TileCost& load_cost(const GemmDesc& g, int t) {
+  const bool chunks = (g.a_kc ? g.K : g.M) % 4 == 0 && (g.b_kc ? g.K : g.N) % 4 == 0;
+  return chunks ? tile_cost(g, t) : kTilesSingle[g.bf16][g.a_kc][t];
+}
 constexpr double kSumLaunch = 4.0, kBytesPerUs = 4.5e6;
 
 struct Plan {
@@ -676,7 +702,7 @@ Plan plan_staged(const GemmDesc& g, double* time = nullptr) {
   Plan best{0, 1};
   double best_cost = -1.0;
   for (int t = 0; t < 3; ++t) {
-    const TileCost& c = tile_cost(g, t);
+    const TileCost& c = load_cost(g, t);
     const SplitRange r = split_range(g, t);
     for (int s = r.lo; s <= r.hi; s = next_split(s)) {
       const Shape h = shape_of(g, t, s);

@@ -149,6 +149,14 @@ def test_gemm_argument_checks():
     assert g(2, 0, 512, 512, 1 << 16, FAKE, 512, FAKE, 512, FAKE, 512, None, 0, None) == E_WS
 
 
+@pytest.mark.parametrize("dtype,M,N,K", [(0, 7064, 405, 670), (1, 3612, 301, 2048),
+                                         (1, 1604, 801, 2000)])
+def test_odd_sums_over_tokens_leave_the_small_tiles(dtype, M, N, K):
+    """Element loads are dearest on the smallest tile, whose workgroups alone
+    fill the chip here: the sum runs on larger tiles, in at least two parts."""
+    assert sru.lib().sru_gemm_workspace_bytes(2, M, N, K, dtype) >= 2 * 4 * M * N
+
+
 def test_scan_argument_checks():
     lib = sru.lib()
     f = lib.sru_scan_forward
