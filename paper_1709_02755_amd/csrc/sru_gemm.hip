@@ -1120,7 +1120,12 @@ double direct_cost(bool mid, bool rc, long long wg, double st) {
   return 3.0 + (n / 2) * 2 * (1.4 + 0.51 * st) + (n % 2) * (2.0 + (rc ? 0.85 : 0.62) * st);
 }
 
-// Tile and split count of a direct product: the least modelled time.  The
+// Tile and split count of a direct product: the least modelled time, K-contiguous
+// ones of fewer than kBigMinSteps K steps on mid tiles.  (There a product is its
+// output, which the one workgroup of a CU writes while nothing else runs: 4653 x
+// 2784 x 32 35 us on big tiles, 15.6 on mid; 1520 x 5472 x 88 36 and 19; 10640 x
+// 1376 x 176 29 and 24; in 130 sizes of at most 5 steps big ones were never ahead
+// by more than 3 %: 1626 x 7168 x 64 17.0 and 17.6.)  The
 // K = tokens product (row-contiguous operands) may be cut over K, and so may
 // a K-contiguous product whose caller asks for it (kc_split: dX of a small
 // batch, whose few tiles would leave most CUs idle), with at least 6 K steps
@@ -1128,6 +1133,7 @@ double direct_cost(bool mid, bool rc, long long wg, double st) {
 // result (Cb) is never split.  E.g. 3072 x 1024 over 16384 tokens: big tiles
 // in 5 splits (240 workgroups of 52 steps, 101 us and 12 for the sum); over
 // 2048: mid tiles in 2 (21 and 6 us; big ones in 5: 25 and 12).
+constexpr int kBigMinSteps = 6;
 struct DirectPlan {
   bool mid;
   int splits;
@@ -1165,7 +1171,7 @@ DirectPlan plan_direct(const GemmDesc& g, double* time = nullptr) {
   const DirectRange r = direct_range(g);
   DirectPlan best{false, r.lo};
   double best_cost = -1.0;
-  for (int m = 0; m < 2; ++m) {
+  for (int m = g.a_kc && kt < kBigMinSteps; m < 2; ++m) {
     const long long tiles = direct_tiles(g, m ? 128 : 256);
     for (int s = r.lo; s <= r.hi; s = next_direct_split(s)) {
       const double cost = direct_cost(m, !g.a_kc, tiles * s, (kt + s - 1) / s) +
