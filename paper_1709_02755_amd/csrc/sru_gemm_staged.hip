@@ -44,9 +44,9 @@
 // Bound by the matrix units where tiles fill the chip (1.3 PFLOP/s of bf16
 // products, what the library's large bf16 products reach), by the latency of
 // a step (load, split, LDS, six dependent products) where they do not.
-// Against the fp32 instruction on 128 x 128 tiles: 16384 x 3072 x 1024 takes 905 -> 515 us,
-// 3072 x 1024 over 16384 tokens 940 -> 557 us with its split sum, 2048 x 768
-// x 256 24.7 -> 13.1 us.
+// Against the fp32 instruction on 128 x 128 tiles: 16384 x 3072 x 1024 takes 905 -> 475 us,
+// 3072 x 1024 over 16384 tokens 940 -> 516 us with its split sum, 2048 x 768
+// x 256 24.7 -> 13.6 us.
 //
 // Every fp32 value is a multiple of 2^-149, but bf16's smallest is 2^-133 and
 // its smallest normal value 2^-126: below 2^-110 the parts would lose bits
@@ -600,9 +600,9 @@ using SingleCfg = FCfg<C::NP, C::BM, C::BN, C::BK, C::WAVES_M, C::WAVES_N,
 // and one for each of several, and what a workgroup's start and end add; a
 // split adds its partials' traffic and the launch that sums them.  From times
 // measured over K 128 .. 16384, M 128 .. 16384.  fp32: 16384 x 3072 x 1024
-// runs at 215 TFLOP/s on Big, 182 on Mid, 129 on Small (the fp32
-// instruction: 114); 2048 x 768 x 256 takes 35, 18.5 and 12.6 us (24); 128 x
-// 384 x 128 24, 12 and 6.1 us (14.3).  bf16 (before: one 256 x 256 tile,
+// runs at 217 TFLOP/s on Big, 182 on Mid, 129 on Small (the fp32
+// instruction: 114); 2048 x 768 x 256 takes 35, 18.5 and 13.6 us (24); 128 x
+// 384 x 128 24, 12 and 6.4 us (14.3).  bf16 (before: one 256 x 256 tile,
 // element-wise loads where rows were no whole 16-byte chunks): 1001 x 1600 x
 // 300 9.1 us (31.5 with fp32 operands, 92 with bf16 ones), 12800 x 900 x 300
 // 27 (35), 4000 x 771 x 257 21 (80), 16384 x 3072 x 1024 143 (208).
