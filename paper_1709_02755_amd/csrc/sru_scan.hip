@@ -899,7 +899,7 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_lin_maps_kernel(ScanSh
   for (int base = sbeg; base < send; base += NW * CH) {
     const int st0 = base + w * CH;
     float r1[CH], r2[CH], rd[CH];
-    bool act[CH];
+    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const long long t = tof(st0 + i < send ? st0 + i : send - 1);
@@ -912,8 +912,10 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_lin_maps_kernel(ScanSh
         rd[i] = 0.0f;
       }
       act[i] = st0 + i < send;
-      if constexpr (MASK) act[i] = act[i] && mp[t * s.B] == 0;
+      pad[i] = MASK ? mp[t * s.B] != 0 : false;
     }
+#pragma unroll
+    for (int i = 0; i < CH; ++i) act[i] = act[i] & !pad[i];
     float Aw = 1.0f, Sw = 0.0f;
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
@@ -985,7 +987,7 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_fwd_lin_kernel(Scan
     const int p = blk & 1;
     const int st0 = base + w * CH;
     float ru0[CH], rf[CH], ru2[CH], rx[CH];
-    bool act[CH];
+    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int st = st0 + i < send ? st0 + i : send - 1;
@@ -997,8 +999,10 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_fwd_lin_kernel(Scan
       if constexpr (KB == 4) rx[i] = __builtin_nontemporal_load(u + 3 * d);
       else rx[i] = xp[t * x_step];
       act[i] = st0 + i < send;
-      if constexpr (MASK) act[i] = act[i] && mp[t * s.B] == 0;
+      pad[i] = MASK ? mp[t * s.B] != 0 : false;
     }
+#pragma unroll
+    for (int i = 0; i < CH; ++i) act[i] = act[i] & !pad[i];
     // 1. this chunk's map
     float A = 1.0f, S = 0.0f;
 #pragma unroll
@@ -1107,7 +1111,7 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_lin_kernel(Scan
     const int p = blk & 1;
     const int i0 = base + w * CH;
     float ru0[CH], rf[CH], rr[CH], rx[CH], rdh[CH], rc[CH + 1];
-    bool act[CH];
+    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
 #pragma unroll
     for (int m = 0; m < CH; ++m) {
       const long long t = tproc(i0 + m);
@@ -1120,8 +1124,10 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_lin_kernel(Scan
       rdh[m] = __builtin_nontemporal_load(dhp + t * h_step);
       rc[m] = cpp[t * h_step];
       act[m] = i0 + m < send;
-      if constexpr (MASK) act[m] = act[m] && mp[t * s.B] == 0;
+      pad[m] = MASK ? mp[t * s.B] != 0 : false;
     }
+#pragma unroll
+    for (int m = 0; m < CH; ++m) act[m] = act[m] & !pad[m];
     {
       const int ie = i0 + CH;  // c_p of the chunk's last step
       rc[CH] = ie < L ? cpp[tproc(ie) * h_step] : c0v;
