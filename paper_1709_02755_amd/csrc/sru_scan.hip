@@ -899,7 +899,10 @@ __global__ __launch_bounds__(64 * kLinMaxWaves) void scan_lin_maps_kernel(ScanSh
   for (int base = sbeg; base < send; base += NW * CH) {
     const int st0 = base + w * CH;
     float r1[CH], r2[CH], rd[CH];
-    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
+    // pad is read whether or not the step is there: under a condition each byte
+    // is waited for before the next step's loads (L 400, B 32, d 128 in both
+    // directions: forward scan 24.0 us so, 18.6 now, backward 39.1 and 31.0)
+    bool act[CH], pad[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const long long t = tof(st0 + i < send ? st0 + i : send - 1);
@@ -987,7 +990,7 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_fwd_lin_kernel(Scan
     const int p = blk & 1;
     const int st0 = base + w * CH;
     float ru0[CH], rf[CH], ru2[CH], rx[CH];
-    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
+    bool act[CH], pad[CH];  // pad: read in any case, as above
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int st = st0 + i < send ? st0 + i : send - 1;
@@ -1111,7 +1114,7 @@ __global__ __launch_bounds__(LW * kLinMaxWaves, 4) void scan_bwd_lin_kernel(Scan
     const int p = blk & 1;
     const int i0 = base + w * CH;
     float ru0[CH], rf[CH], rr[CH], rx[CH], rdh[CH], rc[CH + 1];
-    bool act[CH], pad[CH];  // pad: read whether or not the step is there, so that no load waits
+    bool act[CH], pad[CH];  // pad: read in any case, as above
 #pragma unroll
     for (int m = 0; m < CH; ++m) {
       const long long t = tproc(i0 + m);
